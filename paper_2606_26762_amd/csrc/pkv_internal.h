@@ -18,6 +18,8 @@ constexpr int TMAX = 1024; // tokens per frame
 constexpr int MAXB = 64;   // streams per launch batch
 constexpr int MAX_SPLITS = 16;  // attention context splits (partials storage)
 constexpr int MAX_RBLOCKS = 2;  // query-row blocks of 256 per kv head
+constexpr int F32_KEYS = 32;    // keys per tile of the float32 readout
+constexpr int NUM_SIMD = 1024;  // 256 compute units of four SIMDs
 constexpr int KMAX = 65535;     // prototype slots per unit (slot ids fit 16 bits)
 constexpr int PCW = SMAX + 2;   // words per (slot, K/V) decode record: S tuples, no-residual flag, tau (key record) / n (value record)
 // The bf16 readout forms pseudo-token rows in LDS from at most PS_SLOTS slots

@@ -626,8 +626,22 @@ static protokv_status plan_attend(protokv_t h, int32_t sid, const void* q, int32
   if (ctx == 0) return h->fail(PROTOKV_E_STATE, std::string(who) + ": empty context (no frames appended)");
   const int rows = tq * (h->dm.Hq / h->dm.Hkv);
   int splits;
-  if (h->dm.kv_fp32) splits = std::max(1, std::min(max_splits, (1024 + h->dm.units * rows - 1) / (h->dm.units * rows)));
-  else {
+  if (h->dm.kv_fp32) {
+    // one wave per (kv head, split, 32 query rows) and SIMD: the split count
+    // with the least rounds of waves times tiles per wave, one tile's time
+    // added for a wave's start and its share of the merge
+    const int64_t items = (int64_t)h->dm.units * ((rows + 31) / 32);
+    const int tiles = (ctx + F32_KEYS - 1) / F32_KEYS;
+    int64_t best = INT64_MAX;
+    splits = 1;
+    for (int s = 1; s <= std::min(max_splits, tiles); ++s) {
+      const int64_t cost = (items * s + NUM_SIMD - 1) / NUM_SIMD * ((tiles + s - 1) / s + 1);
+      if (cost < best) { best = cost; splits = s; }
+    }
+    aa.chunk = (tiles + splits - 1) / splits * F32_KEYS;
+    aa.splits = (ctx + aa.chunk - 1) / aa.chunk;
+    return PROTOKV_OK;
+  } else {
     const int rblocks = (rows + 255) / 256;
     // about one workgroup per compute unit (256 on MI355X)
     splits = std::max(1, std::min(max_splits, (256 + h->dm.units * rblocks / 2) / (h->dm.units * rblocks)));

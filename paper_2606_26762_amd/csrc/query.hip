@@ -1301,32 +1301,6 @@ hipError_t launch_materialize(const Dims& dm, const Workspace& ws, int sid, int 
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
 
-struct CtxRef {
-  const uint8_t* base;
-  float bias;
-  bool ok;
-};
-
-template <int ES>
-__device__ __forceinline__ CtxRef ctx_key(const Dims& dm, const Workspace& ws, const AttendArgs& aa,
-                                          size_t unit, int u, int idx, bool values) {
-  CtxRef r;
-  r.ok = idx < aa.n_near + aa.n_far;
-  r.bias = 0.f;
-  if (!r.ok) { r.base = nullptr; return r; }
-  if (idx < aa.n_near) {
-    const int f = aa.f_first + idx / dm.T;
-    const int tok = idx - (idx / dm.T) * dm.T;
-    const int slot = f % (dm.W + 1);
-    r.base = (values ? ws.ring_v : aa.near_k) + (((unit * (dm.W + 1) + slot) * dm.T + tok) * (size_t)D) * ES;
-  } else {
-    const int row = idx - aa.n_near;
-    r.base = (values ? ws.pv : ws.pk) + (((size_t)u * dm.K * dm.S + row) * (size_t)D) * ES;
-    r.bias = aa.rowbias ? aa.rowbias[(size_t)u * dm.K * dm.S + row] : ws.pbias[(size_t)u * dm.K + row / dm.S];
-  }
-  return r;
-}
-
 // bf16 path.  Workgroup = eight waves for one (kv head, context split,
 // block of query rows): one wave per 32 rows for up to 256 rows (KH = 1), or
 // for at most 128 rows two waves per 32 rows, each taking one 32-key half
@@ -1998,45 +1972,210 @@ __global__ __launch_bounds__(256) void k_attend_merge(Dims dm, Workspace ws, Att
   merge_row4<FP32, NSP>(dm, ws, aa, u, r, d4);
 }
 
-// float32 path (small fp32 streams): one wave per (kv head, query row, split),
-// each context key scored by the whole wave (two components per lane).
-__global__ __launch_bounds__(64) void k_attend_f32(Dims dm, Workspace ws, AttendArgs aa, int rows) {
-  const int lane = threadIdx.x;
-  const int split = blockIdx.x % aa.splits;
-  const int r = (blockIdx.x / aa.splits) % rows;
-  const int u = blockIdx.x / (aa.splits * rows);
+// float32 path: S^T = K Q^T and O^T = V^T P on v_mfma_f32_32x32x2_f32 (float32
+// products and sums).  One wave = one work item (kv head, context split, 32
+// query rows), 32 keys per tile, four independent waves per workgroup.  A
+// float32 MFMA holds the matrix core for 64 cycles and takes 4 bytes per lane of
+// each operand, so K and V go straight from global memory into the operand
+// registers, 16 bytes per lane and load, half a tile at a time and two half
+// products ahead; only the query sits in LDS (each lane reads back what it wrote).
+//   K: lane (m = lane % 32, h = lane / 32) loads dims 8 j + 4 h .. + 3 of key m,
+//      so step (j, e) contracts dims 8 j + e (h = 0) and 8 j + 4 + e (h = 1);
+//      Q is laid out the same way.
+//   P: register i of S^T holds key 8 (i / 4) + 4 h + i % 4 of query lane % 32: as
+//      it stands the B operand of a step over the keys 8 (i / 4) + i % 4 (h = 0)
+//      and + 4 (h = 1).
+//   V: for that step lane (m, h) loads dims 4 m .. 4 m + 3 of its half's key; row
+//      m of accumulator b is dim 4 m + b, so the output is stored 16 bytes at a
+//      time.
+// A dot product is the sum of eight 16-dim chains, four and four: its rounding
+// error is that of a pairwise sum (one chain of 64 steps would carry several
+// times as much into the exponent).  Bound by the float32 matrix rate: 32 kv
+// heads x 224 rows x 3 616 keys (13.3 GFLOP) take 149 us, of which the matrix
+// cores are busy 56% (one wave per query row with a shuffled dot product per key
+// took 4 311 us); its error against 64 bits fell from 2.3e-6 to 7e-7.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(1))) const f32x4 gbl_f32x4;
+
+__global__ __launch_bounds__(256, 2) void k_attend_f32(Dims dm, Workspace ws, AttendArgs aa, int rows, int rblocks) {
+  __shared__ f32x4 s_q[4][16][64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int nblk = gridDim.x, per = nblk / 8;
+  // blocks of one kv head land on one XCD (dispatch is round-robin over 8)
+  const int lbid = (int)blockIdx.x < per * 8 ? ((int)blockIdx.x % 8) * per + (int)blockIdx.x / 8 : (int)blockIdx.x;
+  const int item = lbid * 4 + wave;
+  if (item >= dm.units * aa.splits * rblocks) return;  // uniform, and nothing below synchronises waves
+  const int rb = item % rblocks, split = (item / rblocks) % aa.splits, u = item / (rblocks * aa.splits);
   const size_t unit = (size_t)aa.sid * dm.units + u;
   const int grp = dm.Hq / dm.Hkv;
   const int l = u / dm.Hkv, kvh = u % dm.Hkv;
-  const int t = r / grp, gg = r % grp;
-  const float2 qv = reinterpret_cast<const float2*>(reinterpret_cast<const float*>(aa.q) +
-                                                    (((size_t)l * aa.tq + t) * dm.Hq + kvh * grp + gg) * D)[lane];
   const int ctx = aa.n_near + aa.n_far;
   const int c0 = split * aa.chunk, c1 = min(ctx, c0 + aa.chunk);
-  const float scale = LOG2E / sqrtf((float)D);
-  float mrun = -INFINITY, lrun = 0.f, o0 = 0.f, o1 = 0.f;
-  for (int idx = c0; idx < c1; ++idx) {
-    CtxRef kr = ctx_key<4>(dm, ws, aa, unit, u, idx, false);
-    CtxRef vr = ctx_key<4>(dm, ws, aa, unit, u, idx, true);
-    const float2 kv = reinterpret_cast<const float2*>(kr.base)[lane];
-    float dot = qv.x * kv.x + qv.y * kv.y;
+  const int ntiles = (c1 - c0 + F32_KEYS - 1) / F32_KEYS;
+  const int m = lane & 31, half = lane >> 5;
+  const int r = rb * 32 + m;  // query row of this lane
+  const bool rvalid = r < rows;
+  // lanes past the last row repeat row 0 and store nothing
+  const int t = rvalid ? r / grp : 0, gg = rvalid ? r % grp : 0;
+  const size_t orow = ((size_t)l * aa.tq + t) * dm.Hq + kvh * grp + gg;
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) dot += __shfl_xor(dot, o, 64);
-    const float s = dot * scale + kr.bias * LOG2E;
-    const float mnew = fmaxf(mrun, s);
-    const float alpha = exp2f(mrun - mnew);
-    const float p = exp2f(s - mnew);
-    const float2 vv = reinterpret_cast<const float2*>(vr.base)[lane];
-    lrun = lrun * alpha + p;
-    o0 = o0 * alpha + p * vv.x;
-    o1 = o1 * alpha + p * vv.y;
-    mrun = mnew;
+  for (int j = 0; j < 16; ++j)
+    s_q[wave][j][lane] = reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(aa.q) + orow * D)[2 * j + half];
+  // the K and V rows of this lane's key of tile tl (keys past the split repeat
+  // its last one) and the key's bias in log2 units
+  auto resolve = [&](int tl, const float*& kp, const float*& vp, float& bias) {
+    const int idx = c0 + tl * F32_KEYS + m;
+    const int pos = min(idx, c1 - 1);
+    bias = 0.f;
+    if (pos < aa.n_near) {
+      const int fo = pos / dm.T;
+      const size_t row = (unit * (dm.W + 1) + (aa.f_first + fo) % (dm.W + 1)) * dm.T + (pos - fo * dm.T);
+      kp = reinterpret_cast<const float*>(aa.near_k) + row * D;
+      vp = reinterpret_cast<const float*>(ws.ring_v) + row * D;
+    } else {
+      const int pr = pos - aa.n_near;
+      const size_t row = (size_t)u * dm.K * dm.S + pr;
+      kp = reinterpret_cast<const float*>(ws.pk) + row * D;
+      vp = reinterpret_cast<const float*>(ws.pv) + row * D;
+      bias = (aa.rowbias ? aa.rowbias[row] : ws.pbias[(size_t)u * dm.K + pr / dm.S]) * LOG2E;
+    }
+    if (idx >= c1) bias = -INFINITY;
+  };
+  // half h of a tile: dims 64 h .. 64 h + 63 of K; registers 8 h .. 8 h + 7 of V,
+  // register i's key being lane 8 (i / 4) + 4 half + i % 4's
+  auto load_k = [&](const float* kp, int h, f32x4 (&kr)[8]) {
+    gbl_f32x4* p = (gbl_f32x4*)(uintptr_t)kp + half + 16 * h;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) kr[j] = p[2 * j];
+  };
+  // value of register i's key (lane addresses in bytes)
+  auto of_key = [&](int x, int i) {
+    return __builtin_amdgcn_ds_bpermute(16 * half + 4 * (8 * (i >> 2) + (i & 3)), x);
+  };
+  auto load_v = [&](const float* vp, int h, f32x4 (&vr)[8]) {
+    const uint64_t a = reinterpret_cast<uint64_t>(vp);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const uint32_t lo = of_key((int)(uint32_t)a, 8 * h + i), hi = of_key((int)(uint32_t)(a >> 32), 8 * h + i);
+      vr[i] = ((gbl_f32x4*)(uintptr_t)((uint64_t)hi << 32 | lo))[m];
+    }
+  };
+  const float scale = LOG2E / sqrtf((float)D);
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  f32x16 oacc[4] = {zero, zero, zero, zero};
+  float mrun = -INFINITY, lrun = 0.f;  // log2 units; lrun: this half's keys
+  // four chains over the dims of half h
+  auto dots = [&](const f32x4 (&kr)[8], int h) {
+    f32x16 s = zero;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      f32x16 a = zero;
+#pragma unroll
+      for (int j = 2 * g; j < 2 * g + 2; ++j) {
+        const f32x4 qv = s_q[wave][8 * h + j][lane];
+        a = __builtin_amdgcn_mfma_f32_32x32x2f32(kr[j].x, qv.x, a, 0, 0, 0);
+        a = __builtin_amdgcn_mfma_f32_32x32x2f32(kr[j].y, qv.y, a, 0, 0, 0);
+        a = __builtin_amdgcn_mfma_f32_32x32x2f32(kr[j].z, qv.z, a, 0, 0, 0);
+        a = __builtin_amdgcn_mfma_f32_32x32x2f32(kr[j].w, qv.w, a, 0, 0, 0);
+      }
+      s = g ? s + a : a;
+      asm("" : "+v"(s));  // summed here, not after every chain is done
+    }
+    return s;
+  };
+  auto weigh = [&](const f32x4 (&vr)[8], const f32x16& p, int h) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      oacc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[i].x, p[8 * h + i], oacc[0], 0, 0, 0);
+      oacc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[i].y, p[8 * h + i], oacc[1], 0, 0, 0);
+      oacc[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[i].z, p[8 * h + i], oacc[2], 0, 0, 0);
+      oacc[3] = __builtin_amdgcn_mfma_f32_32x32x2f32(vr[i].w, p[8 * h + i], oacc[3], 0, 0, 0);
+    }
+  };
+  // keys past the split have weight 0, but 0 x inf would not be 0
+  auto mask = [&](f32x4 (&vr)[8], const f32x16& bv, int h) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const uint32_t keep = bv[8 * h + i] == -INFINITY ? 0u : ~0u;
+      vr[i].x = __uint_as_float(__float_as_uint(vr[i].x) & keep);
+      vr[i].y = __uint_as_float(__float_as_uint(vr[i].y) & keep);
+      vr[i].z = __uint_as_float(__float_as_uint(vr[i].z) & keep);
+      vr[i].w = __uint_as_float(__float_as_uint(vr[i].w) & keep);
+    }
+  };
+  f32x4 k0[8], k1[8], v0[8], v1[8];
+  const float *kp, *vp;
+  float bias;
+  resolve(0, kp, vp, bias);
+  load_k(kp, 0, k0);
+  load_k(kp, 1, k1);
+  for (int tl = 0; tl < ntiles; ++tl) {
+    load_v(vp, 0, v0);
+    __builtin_amdgcn_sched_barrier(0);
+    f32x16 s = dots(k0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    load_v(vp, 1, v1);
+    __builtin_amdgcn_sched_barrier(0);
+    s = s + dots(k1, 1);
+    // bias of register i's key; -inf past the split
+    f32x16 bv;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) bv[i] = __int_as_float(of_key(__float_as_int(bias), i));
+    // the next tile's keys load while this tile's values are used (past the
+    // last tile the loads repeat it)
+    resolve(min(tl + 1, ntiles - 1), kp, vp, bias);
+    load_k(kp, 0, k0);
+    float tmax = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) tmax = fmaxf(tmax, fmaf(s[i], scale, bv[i]));
+    tmax = fmaxf(tmax, xor32(tmax));
+    const float mnew = fmaxf(mrun, tmax);
+    if (__ballot(!(mnew <= mrun))) {  // uniform
+      const float alpha = __builtin_amdgcn_exp2f(mrun - mnew);
+      lrun *= alpha;
+#pragma unroll
+      for (int b = 0; b < 4; ++b) oacc[b] *= alpha;
+      mrun = mnew;
+    }
+    // relative to the maximum before the bias is added: one rounding at the
+    // size of the difference, not of the logit
+    float part[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      s[i] = __builtin_amdgcn_exp2f(fmaf(s[i], scale, -mrun) + bv[i]);
+      part[i & 3] += s[i];
+    }
+    lrun += (part[0] + part[1]) + (part[2] + part[3]);
+    if (c0 + (tl + 1) * F32_KEYS > c1) {  // uniform: the last tile is short
+      mask(v0, bv, 0);
+      mask(v1, bv, 1);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    weigh(v0, s, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    load_k(kp, 1, k1);
+    __builtin_amdgcn_sched_barrier(0);
+    weigh(v1, s, 1);
   }
+  lrun += xor32(lrun);
+  if (!rvalid) return;
+  // register i of oacc[0..3]: dims 4 mm .. 4 mm + 3 with mm = 8 (i / 4) + 4 half + i % 4
+  const bool whole = aa.splits == 1;
+  const float w = whole ? (lrun > 0.f ? 1.0f / lrun : 0.f) : 1.0f;
   const size_t pr = ((size_t)u * dm.max_splits + split) * dm.max_rows + r;
-  reinterpret_cast<float2*>(ws.part_o + pr * D)[lane] = make_float2(o0, o1);
-  if (lane == 0) {
-    ws.part_ml[pr * 2] = mrun;
-    ws.part_ml[pr * 2 + 1] = lrun;
+  float* out = whole ? reinterpret_cast<float*>(aa.o) + orow * D : ws.part_o + pr * D;
+#pragma unroll
+  for (int i = 0; i < 16; ++i)
+    reinterpret_cast<float4*>(out)[8 * (i >> 2) + 4 * half + (i & 3)] =
+        make_float4(oacc[0][i] * w, oacc[1][i] * w, oacc[2][i] * w, oacc[3][i] * w);
+  if (half == 0) {
+    if (!whole) {
+      ws.part_ml[pr * 2] = mrun;
+      ws.part_ml[pr * 2 + 1] = lrun;
+    } else if (aa.lse) {
+      aa.lse[orow] = (mrun + log2f(lrun)) * LN2;
+    }
   }
 }
 
@@ -2044,7 +2183,8 @@ hipError_t launch_attend(const Dims& dm, const Workspace& ws, const AttendArgs& 
   const int grp = dm.Hq / dm.Hkv;
   const int rows = aa.tq * grp;
   if (dm.kv_fp32) {
-    hipLaunchKernelGGL(k_attend_f32, dim3(dm.units * rows * aa.splits), dim3(64), 0, st, dm, ws, aa, rows);
+    const int rblocks = (rows + 31) / 32, items = dm.units * aa.splits * rblocks;
+    hipLaunchKernelGGL(k_attend_f32, dim3((items + 3) / 4), dim3(256), 0, st, dm, ws, aa, rows, rblocks);
   } else {
     // 8 waves per workgroup: 256 query rows, or at most 128 rows with the
     // tiles' key halves split between wave pairs
@@ -2086,7 +2226,7 @@ hipError_t static_scratch_ptr(void** out) {
 }
 
 hipError_t launch_attend_merge(const Dims& dm, const Workspace& ws, const AttendArgs& aa, hipStream_t st) {
-  if (!dm.kv_fp32 && aa.splits == 1) return hipSuccess;  // the bf16 readout wrote O directly
+  if (aa.splits == 1) return hipSuccess;  // the readout wrote O directly
   const int rows = aa.tq * (dm.Hq / dm.Hkv);
   const int nb = (int)(((size_t)dm.units * rows * (D / 4) + 255) / 256);
   if (dm.kv_fp32)
