@@ -177,19 +177,15 @@ __device__ __forceinline__ U128 mul_u128_u32(const U128& a, uint32_t f) {
   return r;
 }
 
-// Decoding, register path: LPB lanes (2 or 4) per (slot, K/V) beam,
-// 64 / LPB beams per wave, for prototypes whose residual count is at most
-// 65534 (every factor H+1 is below 2^16, so a product of the 8 factors fits
-// in 128 bits) and S <= SM.  Lane q of a beam owns the prefixes e = q,
-// q + LPB, ...  For each subspace the lanes rank the codewords (count desc,
-// code asc) by counting, publish the top R = min(S, C) in order through LDS,
-// and merge: S pops of the best row head (product desc, packed tuple asc),
-// the best found in-lane and then with log2(LPB) DPP exchange steps across
-// the beam's lanes; only the winning row advances.  Same beam (width S) and
+// Decoding with counts above 4094: two lanes per (slot, K/V) beam, 32 beams per
+// wave, for prototypes whose residual count is at most 65534 (every factor H+1
+// is below 2^16, so a product of the 8 factors fits in 128 bits) and S <= SM.
+// Lane q of a beam owns the prefixes e = q, q + 2, ...  For each subspace the
+// lanes sort the codewords (count desc, code asc), publish the top R = min(S, C)
+// in order through LDS, and merge: S pops of the best row head (product desc,
+// packed tuple asc), the best found in-lane and then with a DPP exchange with
+// the beam's other lane; only the winning row advances.  Same beam (width S) and
 // order as decode_top_s.
-//
-// With `centres` it also writes the float32 centre sum / n of the (slot,
-// K/V) (IEEE division) and the slot's bias, for the readout's row forming.
 
 // Exchanges within a quad of lanes (DPP quad_perm, no LDS round trip).
 template <int CTRL>
@@ -201,13 +197,6 @@ __device__ __forceinline__ uint64_t qperm64(uint64_t x) {
   return (uint64_t)qperm<CTRL>((uint32_t)x) | ((uint64_t)qperm<CTRL>((uint32_t)(x >> 32)) << 32);
 }
 constexpr int QP_XOR1 = 0xB1;  // lanes (1, 0, 3, 2)
-constexpr int QP_XOR2 = 0x4E;  // lanes (2, 3, 0, 1)
-// value of lane SRC of this lane's quad
-template <int LPB, int SRC>
-__device__ __forceinline__ uint32_t group_bcast(uint32_t x) {
-  static_assert(LPB == 4, "quad broadcast");
-  return qperm<SRC * 0x55>(x);
-}
 
 // (pa, ca) ranks before (pb, cb), without branches
 __device__ __forceinline__ bool before128b(const U128& pa, uint32_t ca, const U128& pb, uint32_t cb) {
@@ -244,12 +233,13 @@ template <int CTRL> __device__ __forceinline__ U128 pt_perm(const U128& x) {
   return U128{qperm64<CTRL>(x.lo), qperm64<CTRL>(x.hi)};
 }
 
-// The beam merge of k_decode4 for one product type P (uint64_t when every
+// The beam merge (S <= 16, large counts) for one product type P (uint64_t when every
 // product of the wave's beams fits in 64 bits, else U128): products of the
 // factors H+1 compare exactly either way.
-template <int SM, int LPB, typename P>
+template <int SM, typename P>
 __device__ __forceinline__ void decode_beam(uint32_t (*s_rank)[CMAX], const uint32_t* hist, bool mine, int S,
                                             int C, int q, int bq, uint32_t* out) {
+  constexpr int LPB = 2;             // lanes per beam
   constexpr int E = SM / LPB;        // prefixes per lane
   constexpr int KPL = CMAX / LPB;    // codewords per lane
   const int R = S < C ? S : C;
@@ -288,58 +278,40 @@ __device__ __forceinline__ void decode_beam(uint32_t (*s_rank)[CMAX], const uint
       }
     }
     // ranks of the 16 keys (unique: the code is in the low bits)
-    if constexpr (LPB == 2) {
-      // each lane sorts its 8 keys descending (bitonic network), then one
-      // bitonic half-cleaner across the pair (lane 0 keeps the larger of
-      // key[k] and the partner's key[7 - k], lane 1 the smaller) and a
-      // bitonic merge of 8 leave lane 0 with ranks 0..7 and lane 1 with
-      // ranks 8..15, both in order
-      auto cx = [&](int a, int b, bool desc) {
-        const uint32_t x = key[a], y = key[b];
-        const uint32_t hi = x > y ? x : y, lo = x > y ? y : x;
-        key[a] = desc ? hi : lo;
-        key[b] = desc ? lo : hi;
-      };
+    // each lane sorts its 8 keys descending (bitonic network), then one
+    // bitonic half-cleaner across the pair (lane 0 keeps the larger of
+    // key[k] and the partner's key[7 - k], lane 1 the smaller) and a
+    // bitonic merge of 8 leave lane 0 with ranks 0..7 and lane 1 with
+    // ranks 8..15, both in order
+    auto cx = [&](int a, int b, bool desc) {
+      const uint32_t x = key[a], y = key[b];
+      const uint32_t hi = x > y ? x : y, lo = x > y ? y : x;
+      key[a] = desc ? hi : lo;
+      key[b] = desc ? lo : hi;
+    };
 #pragma unroll
-      for (int k = 2; k <= KPL; k <<= 1)
+    for (int k = 2; k <= KPL; k <<= 1)
 #pragma unroll
-        for (int j = k >> 1; j > 0; j >>= 1)
-#pragma unroll
-          for (int i = 0; i < KPL; ++i)
-            if ((i ^ j) > i) cx(i, i ^ j, (i & k) == 0);
-      uint32_t t[KPL];
-#pragma unroll
-      for (int k = 0; k < KPL; ++k) t[k] = qperm<QP_XOR1>(key[KPL - 1 - k]);
-#pragma unroll
-      for (int k = 0; k < KPL; ++k) {
-        const uint32_t hi = key[k] > t[k] ? key[k] : t[k], lo = key[k] > t[k] ? t[k] : key[k];
-        key[k] = q == 0 ? hi : lo;
-      }
-#pragma unroll
-      for (int j = KPL >> 1; j > 0; j >>= 1)
+      for (int j = k >> 1; j > 0; j >>= 1)
 #pragma unroll
         for (int i = 0; i < KPL; ++i)
-          if ((i ^ j) > i) cx(i, i ^ j, true);
+          if ((i ^ j) > i) cx(i, i ^ j, (i & k) == 0);
+    uint32_t t[KPL];
 #pragma unroll
-      for (int i = 0; i < KPL; ++i)
-        if (key[i] != 0u && q * KPL + i < R) s_rank[bq][q * KPL + i] = key[i];
-    } else {
-      int rk[KPL];
+    for (int k = 0; k < KPL; ++k) t[k] = qperm<QP_XOR1>(key[KPL - 1 - k]);
 #pragma unroll
-      for (int i = 0; i < KPL; ++i) rk[i] = 0;
-#pragma unroll
-      for (int i2 = 0; i2 < KPL; ++i2) {
-        const uint32_t others[4] = {group_bcast<LPB, 0>(key[i2]), group_bcast<LPB, 1>(key[i2]),
-                                    group_bcast<LPB, 2>(key[i2]), group_bcast<LPB, 3>(key[i2])};
-#pragma unroll
-        for (int src = 0; src < LPB; ++src)
-#pragma unroll
-          for (int i = 0; i < KPL; ++i) rk[i] += others[src] > key[i] ? 1 : 0;
-      }
-#pragma unroll
-      for (int i = 0; i < KPL; ++i)
-        if (key[i] != 0u && rk[i] < R) s_rank[bq][rk[i]] = key[i];
+    for (int k = 0; k < KPL; ++k) {
+      const uint32_t hi = key[k] > t[k] ? key[k] : t[k], lo = key[k] > t[k] ? t[k] : key[k];
+      key[k] = q == 0 ? hi : lo;
     }
+#pragma unroll
+    for (int j = KPL >> 1; j > 0; j >>= 1)
+#pragma unroll
+      for (int i = 0; i < KPL; ++i)
+        if ((i ^ j) > i) cx(i, i ^ j, true);
+#pragma unroll
+    for (int i = 0; i < KPL; ++i)
+      if (key[i] != 0u && q * KPL + i < R) s_rank[bq][q * KPL + i] = key[i];
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -392,17 +364,9 @@ __device__ __forceinline__ void decode_beam(uint32_t (*s_rank)[CMAX], const uint
         }
         uint32_t who = (uint32_t)(q * E + bj);
         // best of the beam's lanes
-#pragma unroll
-        for (int x = 0; x < (LPB == 4 ? 2 : 1); ++x) {
-          P ov;
-          uint32_t oc, ow;
-          if (x == 0) {
-            ov = pt_perm<QP_XOR1>(bv);
-            oc = qperm<QP_XOR1>(bc); ow = qperm<QP_XOR1>(who);
-          } else {
-            ov = pt_perm<QP_XOR2>(bv);
-            oc = qperm<QP_XOR2>(bc); ow = qperm<QP_XOR2>(who);
-          }
+        {
+          const P ov = pt_perm<QP_XOR1>(bv);
+          const uint32_t oc = qperm<QP_XOR1>(bc), ow = qperm<QP_XOR1>(who);
           const bool t = pt_before(ov, oc, bv, bc);
           bv = pt_sel(t, ov, bv);
           bc = sel32(t, oc, bc);
@@ -457,28 +421,354 @@ __device__ __forceinline__ void decode_beam(uint32_t (*s_rank)[CMAX], const uint
   }
 }
 
-template <int SM, int LPB>
-__global__ __launch_bounds__(256) void k_decode4(Dims dm, Workspace ws, int sid, int n_active, int centres) {
-  static_assert(LPB == 2 || LPB == 4, "lanes per beam");
-  constexpr int E = SM / LPB;        // prefixes per lane
-  constexpr int BPW = 64 / LPB;      // beams per wave
-  constexpr int KPL = CMAX / LPB;    // codewords per lane
-  __shared__ uint32_t s_rank[4][BPW][CMAX];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int q = lane & (LPB - 1), bq = lane / LPB;
-  const int beam = (blockIdx.x * 4 + wave) * BPW + bq;  // ((unit * n_active + slot) * 2 + K/V)
-  const bool bvalid = beam < dm.units * n_active * 2;
-  const int kv = beam & 1, up = bvalid ? beam >> 1 : 0;
-  const int u = up / n_active, p = up % n_active;
-  const size_t unit = (size_t)sid * dm.units + u;
-  const uint8_t* row = ws.bank + (unit * dm.K + p) * ROW;
+// Decoding by halves: the top SM tuples of subspaces 0..3 and of subspaces
+// 4..7, then the top SM of their products (the pairs with (i + 1)(j + 1) <= SM,
+// as above).  A product of four factors below 2^37 is a float64 integer whose
+// 16 low mantissa bits are free: they hold the half's code tuple, inverted, so
+// that a candidate is one float64 product and one OR, and one v_max_f64 /
+// v_min_f64 pair orders two candidates by (product desc, tuple asc).  The
+// codeword ranks come from 16-bit keys (H + 1) << 4 | (15 - c), two subspaces
+// in the halves of one register.  Half products from 2^37 (the four largest
+// counts of a half 600 in the geometric mean) are 64-bit integers above the
+// tuple instead, ordered by compares and selects; counts above 4094 are left to
+// decode_beam.
+//
+// The joined product's ties are broken by the first half's tuple, then the
+// second's, whose order within one first half is its rank j: a tag of 2
+// log2(SM) bits (the tuple's rank among the SM first halves, SM - 1 - j).
+// Products below 2^53 / 2^tag carry it in the mantissa like the others; larger
+// ones (below 2^96) are compared as 54 + 42 bits with the tag below.
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+
+// a <- the first in rank order of a and b, b <- the other
+__device__ __forceinline__ void order2(u16x2& a, u16x2& b) {
+  const u16x2 hi = __builtin_elementwise_max(a, b), lo = __builtin_elementwise_min(a, b);
+  a = hi;
+  b = lo;
+}
+// (raw instructions: fmax / fmin would first quiet operands that are never NaN)
+__device__ __forceinline__ double max64(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ double min64(double a, double b) {
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ void order2(double& a, double& b) {
+  const double hi = max64(a, b), lo = min64(a, b);
+  a = hi;
+  b = lo;
+}
+__device__ __forceinline__ void first2(double& a, double b) { a = max64(a, b); }
+__device__ __forceinline__ void order2(uint64_t& a, uint64_t& b) {
+  const bool sw = b > a;
+  const uint64_t t = a;
+  a = sel64(sw, b, a);
+  b = sel64(sw, t, b);
+}
+__device__ __forceinline__ void first2(uint64_t& a, uint64_t b) { a = sel64(b > a, b, a); }
+// a product of two half products: P >> 42, and the low 42 bits above an 8-bit tag
+struct Wide {
+  uint64_t hi, lo;
+};
+__device__ __forceinline__ void order2(Wide& a, Wide& b) {
+  const bool sw = (b.hi > a.hi) | ((b.hi == a.hi) & (b.lo > a.lo));
+  const Wide t = a;
+  a.hi = sel64(sw, b.hi, a.hi);
+  a.lo = sel64(sw, b.lo, a.lo);
+  b.hi = sel64(sw, t.hi, b.hi);
+  b.lo = sel64(sw, t.lo, b.lo);
+}
+__device__ __forceinline__ void first2(Wide& a, const Wide& b) {
+  const bool sw = (b.hi > a.hi) | ((b.hi == a.hi) & (b.lo > a.lo));
+  a.hi = sel64(sw, b.hi, a.hi);
+  a.lo = sel64(sw, b.lo, a.lo);
+}
+// bitonic sequence a[0..N-1] -> rank order
+template <int N, typename E>
+__device__ __forceinline__ void bitonic(E* a) {
+#pragma unroll
+  for (int j = N / 2; j > 0; j >>= 1)
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if ((i & j) == 0) order2(a[i], a[i + j]);
+}
+// a <- the first N in rank order of a[0..N-1] and b[0..M-1], both in order
+template <int N, int M, typename E>
+__device__ __forceinline__ void keep_top(E (&a)[N], const E (&b)[M]) {
+#pragma unroll
+  for (int i = N - M; i < N; ++i) first2(a[i], b[N - 1 - i]);
+  bitonic<N>(a);
+}
+// Eight keys into rank order (Batcher's odd-even merge sort, 19 exchanges).
+__device__ __forceinline__ void sort8(u16x2* a) {
+  constexpr int X[19][2] = {{0, 1}, {2, 3}, {4, 5}, {6, 7}, {0, 2}, {1, 3}, {4, 6}, {5, 7}, {1, 2}, {5, 6},
+                            {0, 4}, {1, 5}, {2, 6}, {3, 7}, {2, 4}, {3, 5}, {1, 2}, {3, 4}, {5, 6}};
+#pragma unroll
+  for (int i = 0; i < 19; ++i) order2(a[X[i][0]], a[X[i][1]]);
+}
+// The top N of the candidates cand(i, j), i, j < N, in rank order: both
+// factors are in order, so candidate (i, j) has (i + 1)(j + 1) - 1 before it and
+// only those with (i + 1)(j + 1) <= N count.  Each column j (prefixes 0 ..
+// N / (j + 1) - 1) is in order, and so is row 0.
+template <typename E, typename F>
+__device__ __forceinline__ void top_products(E (&r)[8], F cand) {
+#pragma unroll
+  for (int i = 0; i < 8; ++i) r[i] = cand(i, 0);
+  E b[4] = {cand(0, 1), cand(1, 1), cand(2, 1), cand(3, 1)};
+  keep_top(r, b);
+  E c[4] = {cand(0, 2), cand(1, 2), cand(1, 3), cand(0, 3)};
+  bitonic<4>(c);
+  keep_top(r, c);
+  E d[4] = {cand(0, 4), cand(0, 5), cand(0, 6), cand(0, 7)};
+  keep_top(r, d);
+}
+template <typename E, typename F>
+__device__ __forceinline__ void top_products(E (&r)[16], F cand) {
+#pragma unroll
+  for (int i = 0; i < 16; ++i) r[i] = cand(i, 0);
+  {
+    E b[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) b[i] = cand(i, 1);
+    keep_top(r, b);
+  }
+  {  // columns 2 (five), 7 (two)
+    E b[8] = {cand(0, 2), cand(1, 2), cand(2, 2), cand(3, 2), cand(4, 2), E{}, cand(1, 7), cand(0, 7)};
+    bitonic<8>(b);
+    keep_top(r, b);
+  }
+  {  // columns 3 (four), 4 (three)
+    E b[8] = {cand(0, 3), cand(1, 3), cand(2, 3), cand(3, 3), E{}, cand(2, 4), cand(1, 4), cand(0, 4)};
+    bitonic<8>(b);
+    keep_top(r, b);
+  }
+  {  // columns 5, 6 (two each)
+    E b[4] = {cand(0, 5), cand(1, 5), cand(1, 6), cand(0, 6)};
+    bitonic<4>(b);
+    keep_top(r, b);
+  }
+  {
+    E b[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) b[j] = cand(0, 8 + j);
+    keep_top(r, b);
+  }
+}
+
+constexpr double HALF_MAX = 0x1p37;        // half products in float64 stay below this
+constexpr uint32_t HALF_COUNT = 4094;      // counts up to this (half products below 2^48)
+constexpr uint32_t HALF_TAG = 0xFFFFu;     // the inverted tuple in a half product's low bits
+
+__device__ __forceinline__ uint32_t lo32(double x) { return (uint32_t)__double_as_longlong(x); }
+__device__ __forceinline__ uint32_t lo32(uint64_t x) { return (uint32_t)x; }
+__device__ __forceinline__ double with_lo32(double x, uint32_t lo) {
+  return __longlong_as_double((__double_as_longlong(x) & ~0xFFFFFFFFll) | lo);
+}
+__device__ __forceinline__ uint64_t with_lo32(uint64_t x, uint32_t lo) { return (x & ~0xFFFFFFFFull) | lo; }
+// a half product x (tag clear) as an integer
+__device__ __forceinline__ uint64_t half_int(double x) { return (uint64_t)x; }
+__device__ __forceinline__ uint64_t half_int(uint64_t x) { return x >> 16; }
+// the value of lane CTRL's pattern in the quad
+template <int CTRL>
+__device__ __forceinline__ double half_perm(double x) {
+  return __longlong_as_double((long long)qperm64<CTRL>((uint64_t)__double_as_longlong(x)));
+}
+template <int CTRL>
+__device__ __forceinline__ uint64_t half_perm(uint64_t x) { return qperm64<CTRL>(x); }
+
+// The counts of four subspaces, and the largest half product and count they
+// can give.
+struct HalfCounts {
+  uint4 h[4][4];
+  double bound;
+  uint32_t most;
+};
+
+// The top SM tuples of one half, in rank order: product | inverted tuple (E:
+// float64, or uint64_t with the product shifted up by 16).
+template <int SM, typename E>
+__device__ __forceinline__ void decode_half(const HalfCounts& hc, int C, E (&p)[SM]) {
+  using F = std::conditional_t<std::is_same_v<E, double>, double, uint32_t>;
+#pragma unroll
+  for (int pr = 0; pr < 2; ++pr) {  // subspaces 2 pr (low halves) and 2 pr + 1
+    u16x2 key[16];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const uint4 a = hc.h[2 * pr][v], b = hc.h[2 * pr + 1][v];
+      const uint32_t x[4] = {a.x | b.x << 16, a.y | b.y << 16, a.z | b.z << 16, a.w | b.w << 16};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int c = 4 * v + e;
+        const uint32_t k = (x[e] << 4) + (uint32_t)(16 + 15 - c) * 0x10001u;
+        key[c] = __builtin_bit_cast(u16x2, c < C ? k : 0u);
+      }
+    }
+    sort8(key);
+    sort8(key + 8);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if (SM == 16) order2(key[i], key[15 - i]);
+      else key[i] = __builtin_elementwise_max(key[i], key[15 - i]);
+    }
+    bitonic<8>(key);
+    if (SM == 16) {
+      bitonic<8>(key + 8);  // (in reversed places: still a bitonic sequence)
+    }
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int g = 2 * pr + s;
+      F f[SM];
+      uint32_t z[SM];
+#pragma unroll
+      for (int j = 0; j < SM; ++j) {
+        const uint32_t k = __builtin_bit_cast(uint32_t, key[j]);
+        f[j] = (F)((k >> (16 * s + 4)) & 0xFFFu);
+        z[j] = ((k >> (16 * s)) & 15u) << (12 - 4 * g);
+      }
+      if (g == 0) {
+#pragma unroll
+        for (int j = 0; j < SM; ++j) {
+          const E x = (E)f[j] * (E)(std::is_same_v<E, double> ? 1 : 65536);
+          p[j] = with_lo32(x, lo32(x) | z[j]);
+        }
+        continue;
+      }
+      E b[SM];
+      uint32_t t[SM];
+#pragma unroll
+      for (int i = 0; i < SM; ++i) {
+        t[i] = lo32(p[i]) & HALF_TAG;
+        b[i] = with_lo32(p[i], lo32(p[i]) & ~HALF_TAG);
+      }
+      top_products(p, [&](int i, int j) {
+        const E x = b[i] * f[j];
+        return with_lo32(x, lo32(x) | t[i] | z[j]);
+      });
+    }
+  }
+}
+
+// The top S tuples from the halves' top SM (pa: subspaces 0..3, pb: 4..7), lane
+// q of the pair writing those of its parity.  `wide`: uniform, some lane's
+// product may not fit the mantissa beside its tag.  codes: 2 SM words of LDS per
+// lane at a stride of 64 words.
+template <int SM, typename E>
+__device__ __forceinline__ void decode_join(const E (&pa)[SM], const E (&pb)[SM], bool wide, bool mine, int S, int q,
+                                            uint32_t* codes, uint32_t* out) {
+  constexpr int LB = SM == 8 ? 3 : 4;
+  uint32_t ra[SM];  // rank of the first half's tuple among the SM, larger = earlier tuple
+#pragma unroll
+  for (int i = 0; i < SM; ++i) ra[i] = 0;
+#pragma unroll
+  for (int i = 0; i < SM; ++i)
+#pragma unroll
+    for (int k = 0; k < i; ++k) {
+      const uint32_t t = (lo32(pa[k]) & HALF_TAG) < (lo32(pa[i]) & HALF_TAG) ? 1u : 0u;
+      ra[i] += t;
+      ra[k] += 1u - t;
+    }
+  E a[SM], b[SM];
+#pragma unroll
+  for (int i = 0; i < SM; ++i) {
+    codes[ra[i] * 64] = (~lo32(pa[i]) & HALF_TAG) << 16;
+    codes[(2 * SM - 1 - i) * 64] = ~lo32(pb[i]) & HALF_TAG;
+    a[i] = with_lo32(pa[i], lo32(pa[i]) & ~HALF_TAG);
+    b[i] = with_lo32(pb[i], lo32(pb[i]) & ~HALF_TAG);
+    ra[i] <<= LB;
+  }
+  uint32_t tag[SM];
+  bool done = false;
+  if constexpr (std::is_same_v<E, double>) {
+    if (!wide) {
+      double r[SM];
+      top_products(r, [&](int i, int j) {
+        const double x = a[i] * b[j];
+        return with_lo32(x, lo32(x) | ra[i] | (uint32_t)(SM - 1 - j));
+      });
+#pragma unroll
+      for (int o = 0; o < SM; ++o) tag[o] = lo32(r[o]) & (SM * SM - 1);
+      done = true;
+    }
+  }
+  if (!done) {
+    uint64_t ia[SM], ib[SM];
+#pragma unroll
+    for (int i = 0; i < SM; ++i) {
+      ia[i] = half_int(a[i]);
+      ib[i] = half_int(b[i]);
+    }
+    Wide r[SM];
+    top_products(r, [&](int i, int j) {
+      const unsigned __int128 x = (unsigned __int128)ia[i] * ib[j];
+      return Wide{(uint64_t)(x >> 42), ((uint64_t)x & ((1ull << 42) - 1)) << 8 | ra[i] | (uint32_t)(SM - 1 - j)};
+    });
+#pragma unroll
+    for (int o = 0; o < SM; ++o) tag[o] = (uint32_t)r[o].lo & (SM * SM - 1);
+  }
+  if (mine) {
+#pragma unroll
+    for (int o = 0; o < SM; ++o)
+      if (o < S && (o & 1) == q)
+        out[o] = codes[(tag[o] >> LB) * 64] | codes[(SM + (tag[o] & (SM - 1))) * 64];
+    if (q == 0) out[SMAX] = 0u;
+  }
+}
+
+// Two lanes per (slot, K/V) beam, 16 slots per wave: each lane takes a half and
+// both join them.  The wave's histograms (1 KiB per slot) come into LDS by DMA,
+// whole lines at a time: loaded from registers, 16 bytes per lane 256 bytes apart,
+// every line went through L1 several times over.  Lane l of a slot's load brings
+// the 16-byte unit that leaves unit v of (K/V, half) r at 16 r + (v + 4 i + r) %
+// 16, so that lanes reading one unit of different slots fall on different banks.
+// With `centres` (rows formed by the readout) it also writes each slot's bias,
+// tau_k into the key record's spare word and n into the value record's.
+// Bound by the histograms' bytes (256 units x 2 048 slots, 0.6 GB: 159 us, with
+// loads into registers 195, 197 with one lane per beam and sorting networks on
+// 64-bit products) or, on few slots, by one wave's 1 530 VALU instructions
+// (112 units x 256 slots: 32 -> 17 us; 64 slots 25 -> 7 us; S = 16 on 2 000
+// slots, two lanes and merge pops before, 63 -> 13.5 us).
+template <int SM>
+__global__ __launch_bounds__(256) void k_decode(Dims dm, Workspace ws, int sid, int n_active, int centres) {
+  constexpr int SPW = 16;  // slots per wave
+  __shared__ __attribute__((aligned(16))) uint8_t s_mem[4][SPW * 1024];
+  static_assert(2 * SM * 64 * 4 <= SPW * 1024 && 32 * CMAX * 4 <= SPW * 1024, "tuples and ranks reuse the histograms' LDS");
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int nslots = dm.units * n_active;
+  const int slot0 = ((int)blockIdx.x * 4 + wave) * SPW;  // unit * n_active + slot
+  if (slot0 >= nslots) return;  // uniform, and waves do not synchronise below
+  uint8_t* mem = s_mem[wave];
+  const uint8_t* bank = ws.bank + (size_t)sid * dm.units * dm.K * ROW;
+  {
+    int u = slot0 / n_active, p = slot0 % n_active;  // uniform
+#pragma unroll
+    for (int i = 0; i < SPW; ++i) {
+      const int r = lane >> 4, v = ((lane & 15) - (4 * i + r)) & 15;
+      lds_dma16(bank + ((size_t)u * dm.K + p) * ROW + ROW_HK + (16 * r + v) * 16, mem + i * 1024);
+      if (slot0 + i + 1 < nslots) {  // past the last slot the loads repeat it
+        const bool next = p + 1 == n_active;
+        p = next ? 0 : p + 1;
+        u += next ? 1 : 0;
+      }
+    }
+  }
+  const int q = lane & 1, kv = (lane >> 1) & 1;
+  const bool bvalid = slot0 + (lane >> 2) < nslots;
+  const int sl = min(slot0 + (lane >> 2), nslots - 1);
+  const int u = sl / n_active, p = sl % n_active;
+  const uint8_t* row = bank + ((size_t)u * dm.K + p) * ROW;
+  const uint32_t* hist = reinterpret_cast<const uint32_t*>(row + (kv ? ROW_HV : ROW_HK));
   const RowMeta m = *reinterpret_cast<const RowMeta*>(row + ROW_META);
   uint32_t* out = ws.pcodes + (((size_t)u * dm.K + p) * 2 + kv) * PCW;
   const bool pq = (dm.flags & PROTOKV_FLAG_PQ) != 0;
   const int S = dm.S, C = dm.C;
   const bool nores = !pq || m.n_res == 0;
   if (bvalid && q == 0 && nores) out[SMAX] = 1u;
-  if (bvalid && centres && q == 0) {
+  if (centres && bvalid && q == 0) {  // centres: uniform
     if (kv == 0) {
       const bool mb = (dm.flags & PROTOKV_FLAG_MASS_BIAS) != 0;
       ws.pbias[(size_t)u * dm.K + p] = mb ? logf((float)m.n) : 0.f;
@@ -491,272 +781,54 @@ __global__ __launch_bounds__(256) void k_decode4(Dims dm, Workspace ws, int sid,
       out[SMAX + 1] = m.n;
     }
   }
-  // this path decodes the beam (uniform within the beam's lanes)
+  // (k_decode_wide takes the others)
   const bool mine = bvalid && !nores && m.n_res <= 65534u && S <= SM;
-  const uint32_t* hist = reinterpret_cast<const uint32_t*>(row + (kv ? ROW_HV : ROW_HK));
-  // every product the merge forms is at most prod_g max_c (H[g][c] + 1) (the
-  // beam's top tuple); when that fits in 64 bits for all of the wave's
-  // beams the merge runs on 64-bit products
-  bool fits = true;
-  if (mine) {
-    uint64_t bound = 1;
-    bool ovf = false;
+  wait_vm<0>();  // the histograms have landed
+  asm volatile("" ::: "memory");
+  HalfCounts hc;
+  hc.bound = 1.0;
+  hc.most = 0;
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      uint32_t mx = 0;
+  for (int g = 0; g < 4; ++g) {
+    uint32_t mx = 0;
 #pragma unroll
-      for (int v4 = 0; v4 < KPL / 4; ++v4) {
-        const uint4 h4 = reinterpret_cast<const uint4*>(hist + g * CMAX)[q * (KPL / 4) + v4];
-        mx = max(mx, max(max(h4.x, h4.y), max(h4.z, h4.w)));
-      }
-      mx = max(mx, qperm<QP_XOR1>(mx));
-      if (LPB == 4) mx = max(mx, qperm<QP_XOR2>(mx));
-      ovf |= __builtin_mul_overflow(bound, (uint64_t)mx + 1u, &bound);
+    for (int v = 0; v < 4; ++v) {
+      const uint4 x = *reinterpret_cast<const uint4*>(mem + (lane >> 2) * 1024 + (lane & 3) * 256 +
+                                                      ((4 * g + v + lane) & 15) * 16);
+      hc.h[g][v] = x;
+      mx = max(max(mx, max(x.x, x.y)), max(x.z, x.w));
     }
-    fits = !ovf;
+    hc.most = max(hc.most, mx);
+    hc.bound *= (double)mx + 1.0;
   }
-  if (__all(fits))
-    decode_beam<SM, LPB, uint64_t>(s_rank[wave], hist, mine, S, C, q, bq, out);
-  else
-    decode_beam<SM, LPB, U128>(s_rank[wave], hist, mine, S, C, q, bq, out);
-}
-
-// Decoding, one lane per (slot, K/V) beam (S <= 8): the same beam search
-// as decode_beam, with each subspace's merge done by sorting networks in
-// registers.  For S <= 8, the top S of the (prefix i, rank j) products can
-// only come from pairs with (i + 1)(j + 1) <= 8 (every pair (i', j') with
-// i' <= i, j' <= j ranks at least as high: both lists are sorted, and equal
-// products fall back to the packed tuple, whose prefix nibbles lead): the
-// column j = 0 (8 prefixes), j = 1 (4), j = 2 and 3 (2 each), and prefix 0
-// with ranks 4..7.  These sorted lists are merged into the running top 8 by
-// a half-cleaner and a bitonic merger each.
-
-// (pa, ca) and (pb, cb) in rank order (product desc, packed tuple asc)
-template <typename P>
-__device__ __forceinline__ void cx_rank(P& pa, uint32_t& ca, P& pb, uint32_t& cb) {
-  const bool sw = pt_before(pb, cb, pa, ca);
-  const P tp = pa;
-  const uint32_t tc = ca;
-  pa = pt_sel(sw, pb, pa);
-  ca = sel32(sw, cb, ca);
-  pb = pt_sel(sw, tp, pb);
-  cb = sel32(sw, tc, cb);
-}
-// (pa, ca) becomes the first in rank order of a and b
-template <typename P>
-__device__ __forceinline__ void keep_first(P& pa, uint32_t& ca, const P& pb, uint32_t cb) {
-  const bool sw = pt_before(pb, cb, pa, ca);
-  pa = pt_sel(sw, pb, pa);
-  ca = sel32(sw, cb, ca);
-}
-// bitonic sequence of 8 -> rank order
-template <typename P>
-__device__ __forceinline__ void bmerge8(P (&p)[8], uint32_t (&c)[8]) {
+  const double bound = hc.bound * __longlong_as_double((long long)qperm64<QP_XOR1>((uint64_t)__double_as_longlong(hc.bound)));
+  if (__all(!mine || hc.most <= HALF_COUNT)) {
+    const bool wide = !__all(!mine || bound < 0x1p53 / (SM * SM));
+    auto halves = [&](auto e) {
+      using E = decltype(e);
+      E pa[SM], pb[SM];
+      decode_half<SM, E>(hc, C, pa);
 #pragma unroll
-  for (int j = 4; j > 0; j >>= 1)
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-      if ((i & j) == 0) cx_rank(p[i], c[i], p[i + j], c[i + j]);
-}
-// (p, c) <- the first 8 in rank order of (p, c) and (lp, lc), both sorted
-template <int K, typename P>
-__device__ __forceinline__ void merge_top8(P (&p)[8], uint32_t (&c)[8], const P (&lp)[K], const uint32_t (&lc)[K]) {
-#pragma unroll
-  for (int i = 8 - K; i < 8; ++i) keep_first(p[i], c[i], lp[7 - i], lc[7 - i]);
-  bmerge8(p, c);
-}
-// 32-bit keys (unique, larger first): a[0..7] sorted descending
-__device__ __forceinline__ void sort8_desc(uint32_t* a) {
-#pragma unroll
-  for (int k = 2; k <= 8; k <<= 1)
-#pragma unroll
-    for (int j = k >> 1; j > 0; j >>= 1)
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-        if ((i ^ j) > i) {
-          const uint32_t x = a[i], y = a[i ^ j];
-          const uint32_t hi = x > y ? x : y, lo = x > y ? y : x;
-          const bool desc = (i & k) == 0;
-          a[i] = desc ? hi : lo;
-          a[i ^ j] = desc ? lo : hi;
-        }
-}
-
-template <typename P>
-__device__ __forceinline__ void decode_beam1(const uint32_t* hist, bool mine, int S, int C, uint32_t* out) {
-  const int R = S < C ? S : C;
-  P pp[8];
-  uint32_t pc[8];
-  int nb = 0;
-  uint4 hnext[4];
-#pragma unroll
-  for (int v4 = 0; v4 < 4; ++v4) hnext[v4] = mine ? reinterpret_cast<const uint4*>(hist)[v4] : make_uint4(0, 0, 0, 0);
-  for (int g = 0; g < G; ++g) {
-    uint4 hcur[4];
-#pragma unroll
-    for (int v4 = 0; v4 < 4; ++v4) {
-      hcur[v4] = hnext[v4];
-      hnext[v4] = mine && g + 1 < G ? reinterpret_cast<const uint4*>(hist + (g + 1) * CMAX)[v4] : make_uint4(0, 0, 0, 0);
-    }
-    // keys (count << 4 | (15 - c)) + 1, larger = better, 0 = absent; the
-    // first 8 in order: both halves sorted, then a half-cleaner and a merger
-    uint32_t key[16];
-#pragma unroll
-    for (int v4 = 0; v4 < 4; ++v4) {
-      const uint32_t hv[4] = {hcur[v4].x, hcur[v4].y, hcur[v4].z, hcur[v4].w};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int c = 4 * v4 + i;
-        key[c] = c < C ? ((hv[i] << 4) | (uint32_t)(15 - c)) + 1u : 0u;
+      for (int i = 0; i < SM; ++i) {  // lanes (1, 1, 3, 3) and (0, 0, 2, 2) of each quad
+        pb[i] = half_perm<0xF5>(pa[i]);
+        pa[i] = half_perm<0xA0>(pa[i]);
       }
-    }
-    sort8_desc(key);
-    sort8_desc(key + 8);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) key[i] = key[i] > key[15 - i] ? key[i] : key[15 - i];
-#pragma unroll
-    for (int j = 4; j > 0; j >>= 1)
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-        if ((i & j) == 0) {
-          const uint32_t x = key[i], y = key[i + j];
-          key[i] = x > y ? x : y;
-          key[i + j] = x > y ? y : x;
-        }
-    // rank j: factor H + 1 (0 past the R ranks) and codeword
-    uint32_t f[8], z[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const bool ok = j < R && key[j] != 0u;
-      f[j] = ok ? ((key[j] - 1u) >> 4) + 1u : 0u;
-      z[j] = 15u - ((key[j] - 1u) & 15u);
-    }
-    const int shift = 4 * (G - 1 - g);
-    if (g == 0) {
-      // one prefix (the empty tuple): the ranks themselves
-      nb = S < R ? S : R;
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const bool ok = i < nb;
-        pp[i] = pt_from<P>(ok ? f[i] : 0u);
-        pc[i] = ok ? z[i] << shift : 0xFFFFFFFFu;
-      }
-      continue;
-    }
-    // candidate (i, j): product pp[i] f[j] (0 when either is absent),
-    // tuple pc[i] | z[j] << shift
-    auto cand = [&](int i, int j, P& cp, uint32_t& cc) {
-      const bool ok = i < nb && j < R;
-      cp = ok ? pt_mul(pp[i], f[j]) : pt_from<P>(0u);
-      cc = ok ? (pc[i] | (z[j] << shift)) : 0xFFFFFFFFu;
+      decode_join<SM, E>(pa, pb, wide, mine, S, q, reinterpret_cast<uint32_t*>(mem) + lane, out);
     };
-    P rp[8];
-    uint32_t rc[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) cand(i, 0, rp[i], rc[i]);
-    {
-      P lp[4];
-      uint32_t lc[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) cand(i, 1, lp[i], lc[i]);
-      merge_top8<4>(rp, rc, lp, lc);
-    }
-    {
-      // columns 2 and 3 (prefixes 0, 1 each) merged into one sorted list
-      P lp[4];
-      uint32_t lc[4];
-      cand(0, 2, lp[0], lc[0]);
-      cand(1, 2, lp[1], lc[1]);
-      cand(1, 3, lp[2], lc[2]);
-      cand(0, 3, lp[3], lc[3]);
-      cx_rank(lp[0], lc[0], lp[2], lc[2]);
-      cx_rank(lp[1], lc[1], lp[3], lc[3]);
-      cx_rank(lp[0], lc[0], lp[1], lc[1]);
-      cx_rank(lp[2], lc[2], lp[3], lc[3]);
-      merge_top8<4>(rp, rc, lp, lc);
-    }
-    {
-      P lp[4];
-      uint32_t lc[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) cand(0, 4 + j, lp[j], lc[j]);
-      merge_top8<4>(rp, rc, lp, lc);
-    }
-    const int nout = S < nb * R ? S : nb * R;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const bool ok = i < nout;
-      pp[i] = ok ? rp[i] : pt_from<P>(0u);
-      pc[i] = ok ? rc[i] : 0xFFFFFFFFu;
-    }
-    nb = nout;
+    if (__all(!mine || hc.bound < HALF_MAX))
+      halves(0.0);
+    else
+      halves((uint64_t)0);
+    return;
   }
-  if (mine) {
-#pragma unroll
-    for (int o = 0; o < 8; ++o)
-      if (o < S) out[o] = o < nb ? pc[o] : 0u;
-    out[SMAX] = 0u;
-  }
-}
-
-// One lane per (slot, K/V) beam, 64 beams (32 slots) per wave, S <= 8.  With
-// `centres` (rows formed by the readout) it also writes each slot's bias,
-// tau_k into the key record's spare word and n into the value record's.
-__global__ __launch_bounds__(256) void k_decode1(Dims dm, Workspace ws, int sid, int n_active, int centres) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int beam0 = (blockIdx.x * 4 + wave) * 64;
-  const int beam = beam0 + lane;  // (unit * n_active + slot) * 2 + K/V
-  const int nbeams = dm.units * n_active * 2;
-  if (beam0 >= nbeams) return;  // uniform
-  const bool bvalid = beam < nbeams;
-  const int kv = beam & 1, up = bvalid ? beam >> 1 : 0;
-  const int u = up / n_active, p = up % n_active;
-  const size_t unit = (size_t)sid * dm.units + u;
-  const uint8_t* row = ws.bank + (unit * dm.K + p) * ROW;
-  const RowMeta m = *reinterpret_cast<const RowMeta*>(row + ROW_META);
-  uint32_t* out = ws.pcodes + (((size_t)u * dm.K + p) * 2 + kv) * PCW;
-  const bool pq = (dm.flags & PROTOKV_FLAG_PQ) != 0;
-  const int S = dm.S, C = dm.C;
-  const bool nores = !pq || m.n_res == 0;
-  if (bvalid && nores) out[SMAX] = 1u;
-  if (centres && bvalid) {  // centres: uniform
-    if (kv == 0) {
-      const bool mb = (dm.flags & PROTOKV_FLAG_MASS_BIAS) != 0;
-      ws.pbias[(size_t)u * dm.K + p] = mb ? logf((float)m.n) : 0.f;
-      // tau_k in the key record's spare word: the readout rotates the
-      // slot's formed pseudo-keys at it
-      out[SMAX + 1] = (uint32_t)m.tau;
-    } else {
-      // n in the value record's spare word: the readout divides the slot's
-      // sums by it
-      out[SMAX + 1] = m.n;
-    }
-  }
-  const bool mine = bvalid && !nores && m.n_res <= 65534u && S <= 8;
-  const uint32_t* hist = reinterpret_cast<const uint32_t*>(row + (kv ? ROW_HV : ROW_HK));
   // every product the merge forms is at most prod_g max_c (H[g][c] + 1);
   // when that fits in 64 bits for all of the wave's beams the merge runs on
   // 64-bit products
-  bool fits = true;
-  if (mine) {
-    uint64_t bound = 1;
-    bool ovf = false;
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      uint32_t mx = 0;
-#pragma unroll
-      for (int v4 = 0; v4 < 4; ++v4) {
-        const uint4 h4 = reinterpret_cast<const uint4*>(hist + g * CMAX)[v4];
-        mx = max(mx, max(max(h4.x, h4.y), max(h4.z, h4.w)));
-      }
-      ovf |= __builtin_mul_overflow(bound, (uint64_t)mx + 1u, &bound);
-    }
-    fits = !ovf;
-  }
-  if (__all(fits))
-    decode_beam1<uint64_t>(hist, mine, S, C, out);
+  uint32_t(*rank)[CMAX] = reinterpret_cast<uint32_t(*)[CMAX]>(mem);
+  if (__all(!mine || bound < 0x1p63))
+    decode_beam<SM, uint64_t>(rank, hist, mine, S, C, q, lane >> 1, out);
   else
-    decode_beam1<U128>(hist, mine, S, C, out);
+    decode_beam<SM, U128>(rank, hist, mine, S, C, q, lane >> 1, out);
 }
 
 // Decoding, wide path (prototypes with more than 65534 residuals, whose
@@ -766,7 +838,7 @@ __global__ __launch_bounds__(256) void k_decode1(Dims dm, Workspace ws, int sid,
 // [units][K][2][SMAX] (packed tuples, subspace 0 in the top nibble) and a flag
 // word per (slot, K/V): 1 if the slot has no residual statistics.
 template <int SM>
-__global__ __launch_bounds__(64) void k_decode(Dims dm, Workspace ws, int sid, int n_active, int blocks_per_unit) {
+__global__ __launch_bounds__(64) void k_decode_wide(Dims dm, Workspace ws, int sid, int n_active, int blocks_per_unit) {
   extern __shared__ __attribute__((aligned(16))) uint8_t s_dyn[];
   const int lane = threadIdx.x;
   const int u = blockIdx.x / blocks_per_unit;
@@ -779,8 +851,8 @@ __global__ __launch_bounds__(64) void k_decode(Dims dm, Workspace ws, int sid, i
   const RowMeta m = *reinterpret_cast<const RowMeta*>(row + ROW_META);
   uint32_t* out = ws.pcodes + (((size_t)u * dm.K + p) * 2 + kv) * PCW;
   const bool pq = (dm.flags & PROTOKV_FLAG_PQ) != 0;
-  if (!pq || m.n_res == 0) return;             // flagged by k_decode4
-  if (m.n_res <= 65534u && S <= SM) return;    // decoded by k_decode4
+  if (!pq || m.n_res == 0) return;             // flagged by k_decode
+  if (m.n_res <= 65534u && S <= SM) return;    // decoded by k_decode
   out[SMAX] = 0u;
   const uint32_t* hist = reinterpret_cast<const uint32_t*>(row + (kv ? ROW_HV : ROW_HK));
   uint32_t codes[SMAX];
@@ -996,16 +1068,13 @@ hipError_t launch_decode(const Dims& dm, const Workspace& ws, int sid, int n_act
   if (n_active <= 0) return hipSuccess;
   const int bpu = (n_active + SYN_P - 1) / SYN_P;
   const size_t lds = (size_t)2 * dm.S * 64 * (3 * sizeof(uint64_t) + sizeof(uint32_t));
-  const int nbeams = dm.units * n_active * 2;
-  constexpr int LPB = 2;  // lanes per beam
-  const int nblk = (nbeams + 4 * (64 / LPB) - 1) / (4 * (64 / LPB));
+  const dim3 grid((unsigned)((dm.units * n_active + 63) / 64));  // 64 slots per workgroup
   if (dm.S <= 8) {
-    const int nblk1 = (nbeams + 255) / 256;
-    hipLaunchKernelGGL(k_decode1, dim3(nblk1), dim3(256), 0, st, dm, ws, sid, n_active, centres ? 1 : 0);
-    if (wide) hipLaunchKernelGGL(k_decode<8>, dim3(dm.units * bpu), dim3(64), lds, st, dm, ws, sid, n_active, bpu);
+    hipLaunchKernelGGL(k_decode<8>, grid, dim3(256), 0, st, dm, ws, sid, n_active, centres ? 1 : 0);
+    if (wide) hipLaunchKernelGGL(k_decode_wide<8>, dim3(dm.units * bpu), dim3(64), lds, st, dm, ws, sid, n_active, bpu);
   } else {
-    hipLaunchKernelGGL((k_decode4<16, LPB>), dim3(nblk), dim3(256), 0, st, dm, ws, sid, n_active, centres ? 1 : 0);
-    if (wide) hipLaunchKernelGGL(k_decode<16>, dim3(dm.units * bpu), dim3(64), lds, st, dm, ws, sid, n_active, bpu);
+    hipLaunchKernelGGL(k_decode<16>, grid, dim3(256), 0, st, dm, ws, sid, n_active, centres ? 1 : 0);
+    if (wide) hipLaunchKernelGGL(k_decode_wide<16>, dim3(dm.units * bpu), dim3(64), lds, st, dm, ws, sid, n_active, bpu);
   }
   return hipGetLastError();
 }

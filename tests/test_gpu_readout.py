@@ -65,3 +65,67 @@ def test_float32_readout(grp, tq, S, frames):
         torch.cuda.synchronize()
         inf = torch.isinf(o)
         assert bool(inf[0, :, 0, 7].all()) and int(inf.sum()) == tq and not bool(torch.isnan(o).any())
+
+
+def _histograms(kind, C, rng):
+    """[8][C] counts, every subspace with the same total."""
+    if kind == "equal":
+        return np.full((8, C), 3, dtype=np.int64)
+    top = {"collide": 6, "join below 8": 57, "join above 8": 58, "join below 16": 48, "join above 16": 49,
+           "half below": 607, "half above": 608, "wide": 400}.get(kind)
+    if top is not None:   # one count vector, permuted per subspace: products collide
+        base = np.array([top, top - 1, top - 1] + [top * (C - i) // C for i in range(3, C)], dtype=np.int64)[:C]
+        return np.stack([base[rng.permutation(C)] for _ in range(8)])
+    top = {"count below": 4094, "count above": 4095}[kind]   # one subspace peaked, the others even
+    out = np.full((8, C), top // C, dtype=np.int64)
+    out[:, :top % C] += 1
+    out[3] = 0
+    out[3, C // 2] = top
+    return out
+
+
+# S = 8 and 16 are the lists' own lengths; C = 2 has fewer codewords than
+# ranks; 256 units x 260 slots are more beams than two lanes each are used for
+@pytest.mark.parametrize("S,C,units,cap", [(8, 16, 2, 40), (5, 12, 2, 40), (1, 2, 2, 40), (16, 16, 2, 40),
+                                           (9, 2, 2, 40), (8, 16, 256, 260)])
+def test_decode_at_the_edges_of_its_products(S, C, units, cap):
+    """Exact top-S tuples with every slot of a launch on one side of a limit:
+    half products below and above 2^37, joined products below and above the
+    mantissa's room beside the tag, counts of 4094 and 4095, all products
+    equal, products colliding across tuples.  Rows bitwise against the oracle's."""
+    from oracle import protokv_oracle as O
+    h = H()
+    kvh = min(units, 8)
+    wl = W.WORKLOADS["7b"].with_(num_layers=units // kvh, num_kv_heads=kvh, num_q_heads=kvh, grid_h=7, grid_w=7,
+                                 frames=0, window_frames=2, capacity=cap, query_tokens=1)
+    p = h.oracle_params(wl, S=S, C=C, B=max(32, S))
+    cb = W.make_codebooks_device(wl, samples=256, iters=3, C=C)[0]
+    gpu = h.pk.ProtoKV(h.gpu_config(wl, p), cb)
+    gen = W.DeviceStream(wl)
+    while gpu.stream_info(0).active_slots < cap or gpu.stream_info(0).evicted_tokens < 20000:
+        gpu.append_frame([0], *gen.next_frame())
+        gpu.fold()
+    state = gpu.get_state(0)
+    rng = np.random.default_rng(S * 100 + C)
+    sample = [0, units - 1]
+    kinds = ["equal", "collide", "join below 8", "join above 8", "join below 16", "join above 16", "half below",
+             "half above", "wide", "count below", "count above"]
+    for kind in kinds if units == 2 else ["collide", "wide", "half above"]:
+        h.log(f"case: decode limits {kind} S={S} C={C} units={units} K={cap}")
+        bank = state.bank()
+        hist = np.stack([_histograms(kind, C, rng) for _ in range(2 * cap)]).reshape(2, cap, 8, C)
+        for u in range(units):
+            for name, x in (("hist_k", hist[0]), ("hist_v", hist[1])):
+                bank[name][u, :, :, :C] = np.roll(x, u, axis=0)
+            bank["n_res"][u] = hist[0, 0, 0].sum()
+            bank["n"][u] = hist[0, 0, 0].sum() + 1
+        rows = h.pk.encode_bank(bank, units, cap).reshape(units, -1)
+        for u in range(units):
+            state.set_bank_rows(u, rows[u])
+        gpu.set_state(0, state)
+        gpu.synthesize(0)
+        gk, gv, _ = gpu.read_pseudo()
+        for u in sample:
+            ps = O.synthesize(h.bank_from_rows(bank, u, p), cb[u], p)
+            n = len(ps.keys)
+            assert np.array_equal(gk[u][:n], ps.keys) and np.array_equal(gv[u][:n], ps.values), f"{kind} unit {u}"
