@@ -120,6 +120,7 @@ struct Workspace {
   int32_t* ps_count;             // [units][K]: S_k (0 for inactive slots)
   int32_t* ps_off;               // [units][K]: first row of slot k, sum of S_j over j < k
   float* prow_bias;              // [units][K*S]: bias of every pseudo-token row
+  double* ps_var;                // [units][K]: Var(H_k)
 };
 
 enum Counter {

@@ -30,7 +30,7 @@ struct StreamState {
 struct Layout {
   size_t ring_k, ring_v, bank, chat_hi, chat_lo, cmeta, assign, codebooks, cbhn, cbmax;
   size_t pk, pv, pbias, pcodes, part_o, part_ml, counters, touched, ring_kr, qrot, rope_inv, reservoir, ema_res;
-  size_t ps_count, ps_off, prow_bias, total;
+  size_t ps_count, ps_off, prow_bias, ps_var, total;
 };
 
 thread_local std::string g_init_err;
@@ -81,6 +81,7 @@ Layout make_layout(const protokv_config& c) {
   ly.ps_count = take(va ? units * K * 4 : 0);
   ly.ps_off = take(va ? units * K * 4 : 0);
   ly.prow_bias = take(va ? units * K * S * 4 : 0);
+  ly.ps_var = take(va ? units * K * 8 : 0);
   ly.total = off;
   return ly;
 }
@@ -398,6 +399,7 @@ protokv_status protokv_init(const protokv_config* c, const float* codebooks, voi
   ws.ps_count = va ? (int32_t*)(b + ly.ps_count) : nullptr;
   ws.ps_off = va ? (int32_t*)(b + ly.ps_off) : nullptr;
   ws.prow_bias = va ? (float*)(b + ly.prow_bias) : nullptr;
+  ws.ps_var = va ? (double*)(b + ly.ps_var) : nullptr;
   h->st.assign(c->num_streams, StreamState());
 
   // codebooks -> [U][2][G][CMAX][DP] with the codeword axis padded to 16

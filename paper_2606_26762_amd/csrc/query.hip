@@ -5,6 +5,7 @@
 // tokens, mass-aware bias, Eq. attn_logit), Eq. pq and Appendix Algorithms
 // "DecodeTopSResidualModes" and "ProtoKV Query-Time Pseudo-Token Decoding
 // and Attention".
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -1214,139 +1215,187 @@ hipError_t launch_rope_q(const Dims& dm, const Workspace& ws, const void* q, int
 
 // ---------------------------------------------------------------------------
 // Variance-aware pseudo-token counts (appendix "Dynamic Pseudo-Token
-// Allocation").  Workgroup = one (layer, kv head) of stream sid.  Every
-// thread computes Var(H_k) of its slots in float64, in the order the
-// definition sums (sides, subspaces, codewords, dims ascending); one thread
-// takes the sums over slots in slot order (water-filling of the shares over
-// the cap, then cumulative rounding), the others compute the shares.
+// Allocation"), in float64 with every sum in the order the definition gives it.
+// k_alloc_var: Var(H_k), 16 lanes per slot, one per (side, subspace), codewords
+// and dims ascending; the sixteen terms are then added in order.  k_alloc:
+// workgroup = one (layer, kv head); the sums over slots run in slot order in one
+// wave (water-filling of the shares over the cap, then cumulative rounding), their
+// operands read from LDS ahead of the chain of additions; the shares are computed
+// by all threads.  With one thread per slot for the variances and one thread
+// reading and adding slot by slot, 6 units x 333 slots took 210 us; now 27 (the
+// chains of additions are 20 of them).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_alloc(Dims dm, Workspace ws, int sid, int A) {
-  __shared__ double s_var[AL_KMAX];
-  __shared__ double s_x[AL_KMAX];
-  __shared__ uint8_t s_cap[AL_KMAX];
-  __shared__ float s_cb[2 * G * CMAX * DP];
-  __shared__ double s_n2[2 * G * CMAX];
-  __shared__ double s_par[2];   // remaining budget, variance sum of the uncapped
-  __shared__ int s_flag;
-  const int tid = threadIdx.x, u = blockIdx.x;
+constexpr int AV_STRIDE = CMAX * DP + 4;  // floats per (side, subspace) in LDS: 16 of them on 16 different bank quads
+
+__global__ __launch_bounds__(256) void k_alloc_var(Dims dm, Workspace ws, int sid, int A, int blocks_per_unit) {
+  __shared__ __attribute__((aligned(16))) float s_cb[2 * G * AV_STRIDE];
+  __shared__ double s_n2[2 * G][CMAX + 1];
+  const int tid = threadIdx.x;
+  const int u = blockIdx.x / blocks_per_unit, blk = blockIdx.x % blocks_per_unit;
   const size_t unit = (size_t)sid * dm.units + u;
-  const int C = dm.C, S = dm.S, smax = dm.pseudo_max;
   const float* cbk = ws.codebooks + unit * (2 * G * CMAX * DP);
-  for (int i = tid; i < 2 * G * CMAX * DP; i += 256) s_cb[i] = cbk[i];
+  for (int i = tid; i < 2 * G * CMAX * DP; i += 256) s_cb[(i >> 8) * AV_STRIDE + (i & 255)] = cbk[i];
   __syncthreads();
-  if (tid < 2 * G * CMAX) {
+  {
     double n2 = 0.0;
+#pragma unroll
     for (int d = 0; d < DP; ++d) {
-      const double c = (double)s_cb[tid * DP + d];
+      const double c = (double)s_cb[(tid >> 4) * AV_STRIDE + (tid & 15) * DP + d];
       n2 = n2 + c * c;
     }
-    s_n2[tid] = n2;
+    s_n2[tid >> 4][tid & 15] = n2;
   }
   __syncthreads();
-  for (int k = tid; k < A; k += 256) {
+  const int sg = tid & 15, lane0 = (tid & 63) & ~15;
+  const float* cb = s_cb + sg * AV_STRIDE;
+  // 16 slots per pass; every lane of a group runs the same passes
+  for (int k = blk * 16 + (tid >> 4); k < A; k += blocks_per_unit * 16) {
     const uint8_t* row = ws.bank + (unit * dm.K + k) * ROW;
     const uint32_t nres = reinterpret_cast<const RowMeta*>(row + ROW_META)->n_res;
-    double total = 0.0;
-    if (nres > 0) {
-      const double den = (double)nres;
-      for (int side = 0; side < 2; ++side) {
-        const uint32_t* hist = reinterpret_cast<const uint32_t*>(row + (side ? ROW_HV : ROW_HK));
-        for (int g = 0; g < G; ++g) {
-          double e2 = 0.0, mean[DP];
+    const double den = (double)nres;
+    uint32_t h[CMAX];  // K's subspaces, then V's (the histograms are adjacent)
 #pragma unroll
-          for (int d = 0; d < DP; ++d) mean[d] = 0.0;
-          for (int c = 0; c < C; ++c) {
-            const double pc = (double)hist[g * CMAX + c] / den;
-            e2 = e2 + pc * s_n2[(side * G + g) * CMAX + c];
-            const float* cw = s_cb + ((side * G + g) * CMAX + c) * DP;
+    for (int v = 0; v < 4; ++v) {
+      const uint4 x = reinterpret_cast<const uint4*>(row + ROW_HK + sg * CMAX * 4)[v];
+      h[4 * v] = x.x; h[4 * v + 1] = x.y; h[4 * v + 2] = x.z; h[4 * v + 3] = x.w;
+    }
+    double e2 = 0.0, mean[DP];
 #pragma unroll
-            for (int d = 0; d < DP; ++d) mean[d] = mean[d] + pc * (double)cw[d];
-          }
-          double m2 = 0.0;
+    for (int d = 0; d < DP; ++d) mean[d] = 0.0;
 #pragma unroll
-          for (int d = 0; d < DP; ++d) m2 = m2 + mean[d] * mean[d];
-          const double v = e2 - m2;
-          total = total + (v > 0.0 ? v : 0.0);
-        }
+    for (int c = 0; c < CMAX; ++c) {
+      if (c < dm.C) {  // uniform
+        const double pc = (double)h[c] / den;
+        e2 = e2 + pc * s_n2[sg][c];
+#pragma unroll
+        for (int d = 0; d < DP; ++d) mean[d] = mean[d] + pc * (double)cb[c * DP + d];
       }
     }
-    s_var[k] = total;
-    s_cap[k] = 0;
+    double m2 = 0.0;
+#pragma unroll
+    for (int d = 0; d < DP; ++d) m2 = m2 + mean[d] * mean[d];
+    const double x = e2 - m2, v = x > 0.0 ? x : 0.0;
+    double total = 0.0;
+#pragma unroll
+    for (int i = 0; i < 2 * G; ++i) total = total + __shfl(v, lane0 + i, 64);
+    if (sg == 0) ws.ps_var[(size_t)u * dm.K + k] = nres > 0 ? total : 0.0;
   }
+}
+
+// Sums a[0..n) in order, n a multiple of 16 (LDS, the tail zeros), and calls
+// each(k, sum up to and with k).  One wave, every lane the same.
+template <typename F>
+__device__ __forceinline__ double sum_in_order(const double* a, int n, F each) {
+  double next[16], acc = 0.0;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) next[i] = a[i];
+  for (int k = 0; k < n; k += 16) {
+    double cur[16];
+    const int kn = min(k + 16, n - 16);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      cur[i] = next[i];
+      next[i] = a[kn + i];
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      acc = acc + cur[i];
+      each(k + i, acc);
+    }
+  }
+  return acc;
+}
+
+__global__ __launch_bounds__(256) void k_alloc(Dims dm, Workspace ws, int sid, int A) {
+  __shared__ __attribute__((aligned(16))) double s_var[AL_KMAX];  // 0 once capped
+  __shared__ __attribute__((aligned(16))) double s_x[AL_KMAX];
+  __shared__ uint8_t s_cap[AL_KMAX];
+  __shared__ double s_w;
+  __shared__ int s_ncap, s_total;
+  const int tid = threadIdx.x, u = blockIdx.x, lane = tid & 63;
+  const int S = dm.S, smax = dm.pseudo_max, A64 = (A + 63) & ~63;
+  for (int k = tid; k < A64; k += 256) {
+    s_var[k] = k < A ? ws.ps_var[(size_t)u * dm.K + k] : 0.0;
+    s_cap[k] = 0;
+    s_x[k] = 0.0;
+  }
+  if (tid == 0) s_ncap = 0;
+  int32_t* cnt = ws.ps_count + (size_t)u * dm.K;
+  int32_t* off = ws.ps_off + (size_t)u * dm.K;
   __syncthreads();
   const int tot = A * S;
-  __shared__ int s_novar;
-  if (tid == 0) {
-    double w = 0.0;
-    for (int k = 0; k < A; ++k) w += s_var[k];
-    s_novar = w == 0.0 ? 1 : 0;  // no variance at all: every S_k = S
+  bool novar = false;
+  for (int ncap = 0, pass = 0;; ++pass) {  // uniform
+    if (tid < 64) {
+      const double w = sum_in_order(s_var, A64, [](int, double) {});
+      if (tid == 0) s_w = w;
+    }
+    __syncthreads();
+    const double w = s_w, rest = (double)(tot - A - ncap * (smax - 1)), nunc = (double)(A - ncap);
+    if (pass == 0 && w == 0.0) {  // no variance at all: every S_k = S
+      novar = true;
+      break;
+    }
+    for (int k = tid; k < A; k += 256) {
+      double x;
+      if (s_cap[k]) x = (double)smax;
+      else if (w > 0.0) x = 1.0 + rest * s_var[k] / w;
+      else x = 1.0 + rest / nunc;
+      s_x[k] = x;
+      if (!s_cap[k] && x > (double)smax) {
+        s_cap[k] = 1;
+        s_var[k] = 0.0;
+        atomicAdd(&s_ncap, 1);
+      }
+    }
+    __syncthreads();
+    const int now = s_ncap;
+    __syncthreads();
+    if (now == ncap) break;
+    ncap = now;
+  }
+  if (tid < 64) {
+    // cumulative rounding: S_k = floor(X_k + 1/2) - floor(X_(k-1) + 1/2)
+    int prev = 0;
+    double mine = 0.0;
+    if (novar) {
+      prev = tot;
+    } else {
+      sum_in_order(s_x, A64, [&](int k, double X) {
+        mine = (k & 63) == lane ? X : mine;
+        if ((k & 63) == 63) {  // uniform: 64 slots done, lane i holds X of slot k - 63 + i
+          const int cur = (int)floor(mine + 0.5);
+          int before = __shfl_up(cur, 1, 64);
+          if (lane == 0) before = prev;
+          const int slot = k - 63 + lane;
+          if (slot < A) {
+            off[slot] = before;
+            cnt[slot] = cur - before;
+          }
+          prev = __shfl(cur, 63, 64);
+        }
+      });
+    }
+    if (tid == 0) s_total = prev;
   }
   __syncthreads();
-  if (!s_novar) {
-    int ncap = 0;
-    for (;;) {  // uniform: every thread sees the same ncap and flags
-      if (tid == 0) {
-        double w = 0.0;
-        for (int k = 0; k < A; ++k)
-          if (!s_cap[k]) w += s_var[k];
-        s_par[0] = (double)(tot - A - ncap * (smax - 1));
-        s_par[1] = w;
-        s_flag = 0;
-      }
-      __syncthreads();
-      const double rest = s_par[0], w = s_par[1];
-      const double nunc = (double)(A - ncap);
-      for (int k = tid; k < A; k += 256) {
-        double x;
-        if (s_cap[k]) x = (double)smax;
-        else if (w > 0.0) x = 1.0 + rest * s_var[k] / w;
-        else x = 1.0 + rest / nunc;
-        s_x[k] = x;
-        if (!s_cap[k] && x > (double)smax) s_flag = 1;  // every writer stores 1
-      }
-      __syncthreads();
-      const int again = s_flag;
-      __syncthreads();
-      if (!again) break;
-      for (int k = tid; k < A; k += 256)
-        if (!s_cap[k] && s_x[k] > (double)smax) s_cap[k] = 1;
-      __syncthreads();
-      if (tid == 0) {
-        int n = 0;
-        for (int k = 0; k < A; ++k) n += s_cap[k];
-        s_par[0] = (double)n;
-      }
-      __syncthreads();
-      ncap = (int)s_par[0];
-      __syncthreads();
-    }
-  }
-  if (tid == 0) {
-    int32_t* cnt = ws.ps_count + (size_t)u * dm.K;
-    int32_t* off = ws.ps_off + (size_t)u * dm.K;
-    // cumulative rounding: S_k = floor(X_k + 1/2) - floor(X_(k-1) + 1/2)
-    double X = 0.0;
-    long long prev = 0;
-    for (int k = 0; k < A; ++k) {
-      off[k] = (int32_t)prev;
-      if (s_novar) {
-        cnt[k] = S;
-        prev += S;
-        continue;
-      }
-      X += s_x[k];
-      const long long cur = (long long)floor(X + 0.5);
-      cnt[k] = (int32_t)(cur - prev);
-      prev = cur;
-    }
-    for (int k = A; k < dm.K; ++k) {
+  for (int k = tid; k < dm.K; k += 256) {
+    if (k >= A) {
       cnt[k] = 0;
-      off[k] = (int32_t)prev;
+      off[k] = s_total;
+    } else if (novar) {
+      cnt[k] = S;
+      off[k] = k * S;
     }
   }
 }
 
 hipError_t launch_alloc(const Dims& dm, const Workspace& ws, int sid, int n_active, hipStream_t st) {
+  if (n_active > 0) {
+    // about 2048 workgroups, each staging its unit's codebooks once
+    const int bpu = std::max(1, std::min((n_active + 15) / 16, 2048 / dm.units));
+    hipLaunchKernelGGL(k_alloc_var, dim3(dm.units * bpu), dim3(256), 0, st, dm, ws, sid, n_active, bpu);
+  }
   hipLaunchKernelGGL(k_alloc, dim3(dm.units), dim3(256), 0, st, dm, ws, sid, n_active);
   return hipGetLastError();
 }
