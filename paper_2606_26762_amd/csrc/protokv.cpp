@@ -648,6 +648,12 @@ static protokv_status plan_attend(protokv_t h, int32_t sid, const void* q, int32
     // about one workgroup per compute unit (256 on MI355X)
     splits = std::max(1, std::min(max_splits, (256 + h->dm.units * rblocks / 2) / (h->dm.units * rblocks)));
   }
+  if (!h->dm.kv_fp32 && rows <= 32) {
+    // every wave takes 32-key tiles of its own: a split is eight waves
+    const int tiles = (ctx + 31) / 32;
+    aa.splits = std::max(1, std::min(splits, (tiles + 7) / 8));
+    return PROTOKV_OK;
+  }
   auto up64 = [](int x) { return (x + 63) / 64 * 64; };
   if (aa.gen) {
     // pseudo-token rows formed in LDS (bf16): every split takes an equal

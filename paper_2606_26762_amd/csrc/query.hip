@@ -2026,6 +2026,408 @@ __global__ __launch_bounds__(NW * 64, 1) void k_attend_bf16(Dims dm, Workspace w
   }
 }
 
+// bf16 path for at most 32 query rows per kv head (the tokens of an answer).
+// With one block of rows there is nothing for waves to share but the context, so
+// every wave takes tiles of its own, 32 keys each, and nothing synchronises until
+// the end, where the workgroup's eight partial outputs are merged through LDS:
+// with the tiles shared by the workgroup, two of eight waves computed and each
+// tile cost a barrier and the whole load - product - softmax - product chain.
+// Tile t of a kv head goes to wave t mod (8 splits): first the tiles that are
+// loaded (near window; also written pseudo-token rows), then those formed.
+//   Loaded: K rows straight into the A operand (lane (m, h): row m, dims 16 kk +
+//   8 h .. + 7), V rows through registers into the wave's LDS tile (by 32-dim
+//   block) for the transposed reads; the next tile's K and V load meanwhile.
+//   Formed: NSL = min(5, 32 / S) whole slots.  The next tile's sums, records and
+//   biases load into registers meanwhile; the centres sum / n go to LDS once per
+//   slot, then each lane forms its row of K in the A operand and half its row of
+//   V in the LDS tile, with the roundings of k_materialize16.
+// Bound by the bytes read (112 kv heads, 7 rows, 1 568 near keys and 256 slots:
+// 123 MB, 26 us at the rate of a copy) and the forming's arithmetic (14 us by
+// itself): 34.8 us, 66.7 with shared tiles.
+constexpr int A32_W = 8;                       // waves per workgroup
+constexpr int A32_VB = 32 * 64 + 64;           // bytes of one 32-dim block of a V tile (64 of padding: bank spread)
+constexpr int A32_SLOTS = 5;                   // slots per formed tile, at most
+constexpr int A32_CS = 1024 + 64;              // bytes of one slot's centres, K then V (64 of padding)
+constexpr int A32_CW = 80;                     // bytes from codeword to codeword (16 of padding: 16 of them on 16 different bank quads)
+constexpr int A32_CEN = 4 * A32_VB;            // wave's LDS: V tile, centres, records, row biases, rotary table
+constexpr int A32_REC = A32_CEN + A32_SLOTS * A32_CS;
+constexpr int A32_BIAS = A32_REC + 768;        // 5 records of 144 bytes
+constexpr int A32_ROPE = A32_BIAS + 128;
+constexpr int A32_WAVE = A32_ROPE + A32_SLOTS * 512;
+constexpr int A32_LDS = A32_W * A32_WAVE + 2 * G * CMAX * A32_CW;
+static_assert(A32_SLOTS * 2 * PCW * 4 <= 768 && A32_WAVE % 16 == 0 && A32_LDS <= 163840, "LDS layout");
+static_assert(A32_W * 66 * 64 * 4 <= A32_LDS, "the merge reuses the tiles");
+
+// Orders the LDS accesses of one wave's lanes (no instruction: a wave's LDS
+// operations complete in order).
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+__global__ __launch_bounds__(A32_W * 64, 2) void k_attend_rows32(Dims dm, Workspace ws, AttendArgs aa, int rows) {
+  __shared__ __attribute__((aligned(16))) uint8_t s_mem[A32_LDS];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // splits of one kv head land on one XCD (dispatch is round-robin over 8)
+  const int nblk = gridDim.x, per = nblk / 8;
+  const int lbid = (int)blockIdx.x < per * 8 ? ((int)blockIdx.x % 8) * per + (int)blockIdx.x / 8 : (int)blockIdx.x;
+  const int split = lbid % aa.splits, u = lbid / aa.splits;
+  const size_t unit = (size_t)aa.sid * dm.units + u;
+  const int grp = dm.Hq / dm.Hkv;
+  const int l = u / dm.Hkv, kvh = u % dm.Hkv;
+  const int m = lane & 31, half = lane >> 5;
+  const bool rvalid = m < rows;
+  const int rt = rvalid ? m / grp : 0, gg = rvalid ? m % grp : 0;
+  const size_t orow = ((size_t)l * aa.tq + rt) * dm.Hq + kvh * grp + gg;
+  uint8_t* mem = s_mem + wave * A32_WAVE;
+  uint8_t* s_cb = s_mem + A32_W * A32_WAVE;  // [K/V][subspace][codeword] at A32_CW
+  const int w0 = split * A32_W + wave, nw = aa.splits * A32_W;  // this wave's tiles: w0, w0 + nw, ...
+  const int nload = aa.gen ? aa.n_near : aa.n_near + aa.n_far;
+  const int ltiles = (nload + 31) / 32;
+  const int nsl = aa.gen ? min(A32_SLOTS, 32 / dm.S) : 1;
+  const int nact = aa.gen ? aa.n_far / dm.S : 0;
+  const int ftiles = (nact + nsl - 1) / nsl;
+  const bool ema = (dm.flags & PROTOKV_FLAG_EMA_CENTRES) != 0;
+  const bool rope = ws.rope_inv != nullptr;  // uniform
+
+  // the unit's codebooks (two 16-byte parts per thread), the query, and below the
+  // first tiles: all loads in flight before the first wait
+  constexpr int CBP = 2 * G * CMAX * DP / 4 / (A32_W * 64);
+  float4 cbr[CBP];
+#pragma unroll
+  for (int i = 0; i < CBP; ++i)
+    cbr[i] = reinterpret_cast<const float4*>(ws.codebooks + unit * (2 * G * CMAX * DP))[tid + i * A32_W * 64];
+  bf16x8 bq[8];
+  {
+    const u16x8* qr = reinterpret_cast<const u16x8*>(reinterpret_cast<const uint16_t*>(aa.q) + orow * D);
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) bq[kk] = __builtin_bit_cast(bf16x8, qr[2 * kk + half]);  // lanes past the rows repeat row 0
+  }
+
+  const float scale = LOG2E / sqrtf((float)D);
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  f32x16 oacc[4] = {zero, zero, zero, zero};
+  float mref = -1e30f, lrun = 0.f;  // as in k_attend_bf16
+  const int grp16 = lane >> 4, s16 = lane & 15;
+  const uint8_t* vl = mem + (4 * half + (s16 >> 2)) * 64 + (grp16 & 1) * 32 + (s16 & 3) * 8;
+  const float4* s_bias = reinterpret_cast<const float4*>(mem + A32_BIAS);
+  const bf16x2 ones2 = {(__bf16)1.0f, (__bf16)1.0f};
+
+  // softmax of the scores s (S^T of 32 keys) and O^T += V^T P from the LDS tile
+  auto weigh = [&](f32x16 s, bool biased) {
+    float tmax = -1e30f;
+    if (biased) {  // uniform
+#pragma unroll
+      for (int i4 = 0; i4 < 4; ++i4) {
+        const float4 b4 = s_bias[i4 * 2 + half];
+        const float bv[4] = {b4.x, b4.y, b4.z, b4.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[i4 * 4 + e] = fmaf(s[i4 * 4 + e], scale, bv[e]);
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 16; ++i) s[i] *= scale;
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) tmax = fmaxf(tmax, s[i]);
+    tmax = fmaxf(tmax, xor32(tmax));
+    const bool grow = tmax > mref + 8.0f;
+    if (__ballot(grow)) {  // uniform
+      const float mnew = grow ? tmax : mref;
+      const float alpha = __builtin_amdgcn_exp2f(mref - mnew);
+      lrun *= alpha;
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) oacc[b][i] *= alpha;
+      mref = mnew;
+    }
+    bf16x8 pb[2];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) pb[i >> 3][i & 7] = (__bf16)__builtin_amdgcn_exp2f(s[i] - mref);
+    float sum0 = 0.f, sum1 = 0.f;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      sum0 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb[j], pb[j], 0, 1), ones2, sum0, false);
+      sum1 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb[j], pb[j], 2, 3), ones2, sum1, false);
+      sum0 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb[j], pb[j], 4, 5), ones2, sum0, false);
+      sum1 = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pb[j], pb[j], 6, 7), ones2, sum1, false);
+    }
+    lrun += sum0 + sum1;  // this half's keys
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int st = 0; st < 2; ++st) {
+        const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(vl + b * A32_VB + st * 1024));
+        const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(vl + b * A32_VB + st * 1024 + 512));
+        const v8i16 a = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        oacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), pb[st], oacc[b], 0, 0, 0);
+      }
+  };
+
+  // formed tiles: this tile's inputs in registers (sums: unit `lane` of slot
+  // i's 64; records: words lane, lane + 64, lane + 128; bias of slot m)
+  const size_t ubase = (size_t)u * dm.K;
+  auto load_slots = [&](int ft, float4 (&fs)[A32_SLOTS], uint32_t (&fr)[3], float& fb) {
+    const int k0 = ft * nsl, last = nact - 1;
+#pragma unroll
+    for (int i = 0; i < A32_SLOTS; ++i)
+      if (i < nsl)  // uniform
+        fs[i] = reinterpret_cast<const float4*>(ws.bank + (unit * dm.K + min(k0 + i, last)) * ROW + ROW_SUMK)[lane];
+#pragma unroll
+    for (int i = 0; i < 3; ++i)  // past the last slot: its value record's last word, n
+      fr[i] = ws.pcodes[ubase * 2 * PCW + min(k0 * 2 * PCW + lane + 64 * i, nact * 2 * PCW - 1)];
+    fb = ws.pbias[ubase + min(k0 + min(m, nsl - 1), last)];
+  };
+
+  // loaded tiles
+  auto row_of = [&](int t, float& bias) {  // ring row, or -1 - pseudo-token row, of this lane's key m
+    const int idx = t * 32 + m, pos = min(idx, nload - 1);
+    int row;
+    bias = 0.f;
+    if (pos < aa.n_near) {
+      const int fo = pos / dm.T;
+      row = ((aa.f_first + fo) % (dm.W + 1)) * dm.T + (pos - fo * dm.T);
+    } else {
+      const int pr = pos - aa.n_near;
+      row = -1 - pr;
+      bias = (aa.rowbias ? aa.rowbias[ubase * dm.S + pr] : ws.pbias[ubase + pr / dm.S]) * LOG2E;
+    }
+    if (idx >= nload) bias = -INFINITY;
+    return row;
+  };
+  const u16x8* nk = reinterpret_cast<const u16x8*>(aa.near_k + unit * (dm.W + 1) * dm.T * (size_t)(D * 2));
+  const u16x8* nv = reinterpret_cast<const u16x8*>(ws.ring_v + unit * (dm.W + 1) * dm.T * (size_t)(D * 2));
+  const u16x8* pk = reinterpret_cast<const u16x8*>(ws.pk + ubase * dm.S * (size_t)(D * 2));
+  const u16x8* pv = reinterpret_cast<const u16x8*>(ws.pv + ubase * dm.S * (size_t)(D * 2));
+  auto load_k = [&](int row, u16x8 (&kr)[8]) {
+    const u16x8* p = row >= 0 ? nk + (size_t)row * 16 : pk + (size_t)(-1 - row) * 16;
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) kr[kk] = p[2 * kk + half];
+  };
+  auto load_v = [&](int row, u16x8 (&vr)[8]) {  // unit i: row 4 i + lane / 16, 16-byte chunk lane % 16
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int r = __builtin_amdgcn_ds_bpermute(4 * (lane >> 4) + 16 * i, row);
+      vr[i] = (r >= 0 ? nv + (size_t)r * 16 : pv + (size_t)(-1 - r) * 16)[lane & 15];
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < CBP; ++i) {
+    const int x = tid + i * A32_W * 64;
+    *reinterpret_cast<float4*>(s_cb + (x >> 2) * A32_CW + (x & 3) * 16) = cbr[i];
+  }
+  // formed tiles: row m is pseudo-token s2 of the tile's slot j
+  const int j = min(m / dm.S, nsl - 1), s2 = m - j * dm.S;
+  // this lane's chunks: of K 2 kk + half, of V 8 half + e
+  const uint8_t* cenk = mem + A32_CEN + j * A32_CS + half * 32;
+  const uint8_t* cenv = mem + A32_CEN + j * A32_CS + 512 + half * 256;
+  const uint8_t* cbk = s_cb + half * 32;
+  const uint8_t* cbv = s_cb + (G + half * 4) * CMAX * A32_CW;
+  const uint32_t* rec = reinterpret_cast<const uint32_t*>(mem + A32_REC) + j * 2 * PCW;
+  const double rinv = rope ? ws.rope_inv[lane] : 0.0;
+  auto loaded_tiles = [&](bool first) {
+    u16x8 kr[8], vr[8];
+    int t = w0, row = 0;
+    float bias = 0.f;
+    if (t < ltiles) {
+      row = row_of(t, bias);
+      load_v(row, vr);
+      load_k(row, kr);
+    }
+    if (first) lds_barrier();  // the codebooks are staged
+    for (; t < ltiles; t += nw) {
+      const int tn = t + nw < ltiles ? t + nw : t;  // past the last tile the loads repeat it
+      float nbias;
+      row = row_of(tn, nbias);
+      const bool biased = (t + 1) * 32 > aa.n_near;  // uniform
+      {
+        if ((t + 1) * 32 > nload) {  // uniform: keys past the context have weight 0, but 0 x inf would not be 0
+#pragma unroll
+          for (int i = 0; i < 8; ++i)
+            if (t * 32 + 4 * i + (lane >> 4) >= nload) vr[i] = (u16x8)0;
+        }
+        uint8_t* vw = mem + ((lane & 15) >> 2) * A32_VB + (lane >> 4) * 64 + (lane & 3) * 16;
+        wave_lds_order();
+#pragma unroll
+        for (int i = 0; i < 8; ++i) *reinterpret_cast<u16x8*>(vw + i * 256) = vr[i];
+        if (biased && half == 0) reinterpret_cast<float*>(mem + A32_BIAS)[m] = bias;
+        wave_lds_order();
+      }
+      load_v(row, vr);
+      f32x16 s = zero;
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk)
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kr[kk]), bq[kk], s, 0, 0, 0);
+      load_k(row, kr);
+      weigh(s, biased);
+      bias = nbias;
+    }
+  };
+  auto formed_tiles = [&](bool first) {
+    float4 fs[A32_SLOTS];
+    uint32_t fr[3];
+    float fb = 0.f;
+    int ft = ((w0 - ltiles) % nw + nw) % nw;  // tile ltiles + ft = w0 mod nw
+    if (ft < ftiles) load_slots(ft, fs, fr, fb);
+    if (first) lds_barrier();
+    for (; ft < ftiles; ft += nw) {
+      wave_lds_order();
+      // centres sum / n (IEEE division)
+#pragma unroll
+      for (int i = 0; i < A32_SLOTS; ++i) {
+        if (i < nsl) {  // uniform
+          constexpr int LAST = PCW + SMAX + 1;  // n in the value record, tau in the key record
+          const int wn = i * 2 * PCW + LAST, wt = i * 2 * PCW + SMAX + 1;
+          const float nf = ema ? 1.f : (float)(uint32_t)__builtin_amdgcn_readlane((int)fr[wn >> 6], wn & 63);
+          reinterpret_cast<float4*>(mem + A32_CEN + i * A32_CS)[lane] =
+              make_float4(fs[i].x / nf, fs[i].y / nf, fs[i].z / nf, fs[i].w / nf);
+          if (rope) {
+            float c, sn;
+            rope_cs((double)__builtin_amdgcn_readlane((int)fr[wt >> 6], wt & 63), rinv, c, sn);
+            reinterpret_cast<float2*>(mem + A32_ROPE)[i * 64 + lane] = make_float2(c, sn);
+          }
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        const int w = lane + 64 * i;
+        if (w < A32_SLOTS * 2 * PCW) reinterpret_cast<uint32_t*>(mem + A32_REC)[w] = fr[i];
+      }
+      const bool ok = m < nsl * dm.S && ft * nsl + j < nact;  // row m is a pseudo-token
+      {
+        const float b = __shfl(fb, j, 64) * LOG2E;
+        if (half == 0) reinterpret_cast<float*>(mem + A32_BIAS)[m] = ok ? b : -INFINITY;
+      }
+      wave_lds_order();
+      if (ft + nw < ftiles) load_slots(ft + nw, fs, fr, fb);
+      const bool tail = nsl * dm.S < 32 || (ft + 1) * nsl > nact;  // uniform
+      // rows past the tile's last slot repeat a valid tuple (bias -inf)
+      const int sv = min(s2, dm.S - 1);
+      const uint32_t tk = rec[sv], tv = rec[PCW + sv] >> (16 - 16 * half);  // V: this half's four subspaces
+      const float mk = rec[SMAX] != 0u ? 0.f : 1.f, mv = rec[PCW + SMAX] != 0u ? 0.f : 1.f;  // no residual: the centre alone
+      // 8 values at centre c, codeword w: exactly c + w or (mul 0) c
+      auto chunk = [&](const uint8_t* c, const uint8_t* w, float mul, float (&x)[8]) {
+        const float4 ca = reinterpret_cast<const float4*>(c)[0], cb = reinterpret_cast<const float4*>(c)[1];
+        const float4 wa = reinterpret_cast<const float4*>(w)[0], wb = reinterpret_cast<const float4*>(w)[1];
+        x[0] = fmaf(wa.x, mul, ca.x); x[1] = fmaf(wa.y, mul, ca.y); x[2] = fmaf(wa.z, mul, ca.z); x[3] = fmaf(wa.w, mul, ca.w);
+        x[4] = fmaf(wb.x, mul, cb.x); x[5] = fmaf(wb.y, mul, cb.y); x[6] = fmaf(wb.z, mul, cb.z); x[7] = fmaf(wb.w, mul, cb.w);
+      };
+      auto keyc = [&](int kk, float (&x)[8]) {  // dims 16 kk + 8 half .. + 7
+        chunk(cenk + kk * 64, cbk + kk * CMAX * A32_CW + ((tk >> (4 * (G - 1 - kk))) & 15) * A32_CW, mk, x);
+      };
+      auto round8 = [](const float (&x)[8]) {
+        bf16x8 r;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) r[e] = (__bf16)x[e];
+        return r;
+      };
+      f32x16 s = zero;
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        // chunks of rotate-half pairs: dims i and i + D / 2
+        float x1[8], x2[8];
+        keyc(kk, x1);
+        keyc(kk + 4, x2);
+        bf16x8 a1 = round8(x1), a2 = round8(x2);
+        if (rope) {  // each key, rounded to bf16 as written, turned at tau_k and rounded again
+          const float4* cs = reinterpret_cast<const float4*>(mem + A32_ROPE) + (j * 64 + 16 * kk + 8 * half) / 2;
+#pragma unroll
+          for (int e2 = 0; e2 < 4; ++e2) {
+            const float4 c4 = cs[e2];  // (cos, sin) of two pairs
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+              const int e = 2 * e2 + h;
+              rope_pair((float)a1[e], (float)a2[e], h ? c4.z : c4.x, h ? c4.w : c4.y, x1[e], x2[e]);
+            }
+          }
+          a1 = round8(x1);
+          a2 = round8(x2);
+        }
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, bq[kk], s, 0, 0, 0);
+        s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a2, bq[kk + 4], s, 0, 0, 0);
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        float x[8];
+        chunk(cenv + e * 32, cbv + (e >> 1) * CMAX * A32_CW + (e & 1) * 32 + ((tv >> (12 - 4 * (e >> 1))) & 15) * A32_CW, mv, x);
+        if (tail) {
+#pragma unroll
+          for (int y = 0; y < 8; ++y) x[y] = ok ? x[y] : 0.f;  // (0 x inf, as above)
+        }
+        *reinterpret_cast<bf16x8*>(mem + (2 * half + (e >> 2)) * A32_VB + m * 64 + (e & 3) * 16) = round8(x);
+      }
+      wave_lds_order();
+      weigh(s, true);
+    }
+  };
+  // Waves w and w + 4 share a SIMD: one takes the loaded tiles first, the other the
+  // formed ones, so that the one's memory latency meets the other's arithmetic
+  // (all loaded tiles first: 37.8 us against 34.8).
+  if (wave < A32_W / 2) {  // uniform
+    loaded_tiles(true);
+    formed_tiles(false);
+  } else {
+    formed_tiles(true);
+    loaded_tiles(false);
+  }
+
+  // merge of the eight waves (each relative to its own reference)
+  lrun += xor32(lrun);
+  __syncthreads();  // the tiles' LDS is reused
+  float* part = reinterpret_cast<float*>(s_mem);
+  if (rvalid) {
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) part[(wave * 66 + b * 16 + i) * 64 + lane] = oacc[b][i];
+    part[(wave * 66 + 64) * 64 + lane] = mref;
+    part[(wave * 66 + 65) * 64 + lane] = lrun;
+  }
+  __syncthreads();
+  if (!rvalid) return;
+  float M = -INFINITY, L = 0.f, wgt[A32_W];
+#pragma unroll
+  for (int w = 0; w < A32_W; ++w) M = fmaxf(M, part[(w * 66 + 64) * 64 + lane]);
+#pragma unroll
+  for (int w = 0; w < A32_W; ++w) {
+    wgt[w] = __builtin_amdgcn_exp2f(part[(w * 66 + 64) * 64 + lane] - M);
+    L += wgt[w] * part[(w * 66 + 65) * 64 + lane];
+  }
+  // wave w's registers 8 w .. 8 w + 7: two runs of four dims
+  const bool whole = aa.splits == 1;
+  const float inv = whole ? (L > 0.f ? 1.0f / L : 0.f) : 1.0f;
+  const size_t prow = ((size_t)u * dm.max_splits + split) * dm.max_rows + m;
+#pragma unroll
+  for (int run = 0; run < 2; ++run) {
+    float o[4];
+    const int i0 = wave * 8 + run * 4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      o[e] = 0.f;
+#pragma unroll
+      for (int w = 0; w < A32_W; ++w) o[e] += wgt[w] * part[(w * 66 + i0 + e) * 64 + lane];
+    }
+    const int dim = (i0 >> 4) * 32 + ((i0 & 15) >> 2) * 8 + half * 4;
+    if (whole)
+      *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(aa.o) + orow * D + dim) =
+          make_uint2((uint32_t)q_to_bf16(o[0] * inv) | ((uint32_t)q_to_bf16(o[1] * inv) << 16),
+                     (uint32_t)q_to_bf16(o[2] * inv) | ((uint32_t)q_to_bf16(o[3] * inv) << 16));
+    else
+      *reinterpret_cast<float4*>(ws.part_o + prow * D + dim) = make_float4(o[0], o[1], o[2], o[3]);
+  }
+  if (wave == 0 && half == 0) {
+    if (!whole) {
+      ws.part_ml[prow * 2] = M;
+      ws.part_ml[prow * 2 + 1] = L;
+    } else if (aa.lse) {
+      aa.lse[orow] = (M + log2f(L)) * LN2;
+    }
+  }
+}
+
 // Combines the splits of each query row: O = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
 // Combines the splits' partials of output row r, dims 4 d4 .. 4 d4 + 3, of
 // kv head u: O = sum_s w_s O_s / sum_s w_s l_s with w_s = 2^(m_s - max m).
@@ -2307,7 +2709,9 @@ hipError_t launch_attend(const Dims& dm, const Workspace& ws, const AttendArgs& 
     // 8 waves per workgroup: 256 query rows, or at most 128 rows with the
     // tiles' key halves split between wave pairs
     const int rblocks = (rows + AT_ROWS - 1) / AT_ROWS;
-    if (rows > 128)
+    if (rows <= 32)
+      hipLaunchKernelGGL(k_attend_rows32, dim3(dm.units * aa.splits), dim3(A32_W * 64), 0, st, dm, ws, aa, rows);
+    else if (rows > 128)
       hipLaunchKernelGGL((k_attend_bf16<8, 1>), dim3(dm.units * aa.splits * rblocks), dim3(512), 0, st, dm, ws, aa,
                          rows, rblocks);
     else

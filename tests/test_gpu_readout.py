@@ -129,3 +129,41 @@ def test_decode_at_the_edges_of_its_products(S, C, units, cap):
             ps = O.synthesize(h.bank_from_rows(bank, u, p), cb[u], p)
             n = len(ps.keys)
             assert np.array_equal(gk[u][:n], ps.keys) and np.array_equal(gv[u][:n], ps.values), f"{kind} unit {u}"
+
+
+# rows per kv head 1, 32 and 9; formed tiles of 5 slots x 5, 6 and of 3 x 9 (the
+# rest of the 32 rows masked), last tiles of 2, 1 and 1 slots; loaded contexts of
+# 105 (last tile of 9 keys) and, without a bank, 70
+@pytest.mark.parametrize("grp,tq,S,cap,frames,theta", [(1, 1, 5, 37, 12, 0.0), (8, 4, 6, 36, 12, 1e4),
+                                                       (3, 3, 9, 31, 12, 0.0), (1, 9, 8, 37, 2, 0.0)])
+def test_few_row_readout(grp, tq, S, cap, frames, theta):
+    """bf16 readout of at most 32 query rows per kv head, pseudo-token rows formed
+    in the wave and then written, against the oracle; without a bank an infinite
+    value in the last key reaches its own dim and no other."""
+    import torch
+    h = H()
+    wl = W.WORKLOADS["7b"].with_(num_layers=3, num_kv_heads=1, num_q_heads=grp, grid_h=5, grid_w=7, frames=frames,
+                                 window_frames=3, capacity=cap, query_tokens=tq)
+    h.log(f"case: few rows {grp * tq} S={S} K={cap} frames {frames} theta {theta}")
+    pair = _stream(h, wl, S=S, B=max(32, S), rope_theta=theta)
+    q = pair.query(np.random.default_rng(S))
+    pseudo = pair.oracle[0].synthesize()
+    oo, ol = pair.oracle[0].attend(q, wl.num_kv_heads, pseudo)
+    qd = torch.from_numpy(q).to("cuda", torch.bfloat16).contiguous()
+    pair.gpu.synthesize(0)
+    for form in ("formed", "written"):
+        o, lse = pair.gpu.attend(0, qd)
+        torch.cuda.synchronize()
+        err, el = np.abs(o.float().cpu().numpy() - oo).max(), np.abs(lse.cpu().numpy() - ol).max()
+        h.log(f"{form} rows: err {err:.2e}, lse {el:.2e}")
+        assert err <= h.READOUT_ATOL and el <= h.LSE_ATOL
+        pair.gpu.read_pseudo()   # writes the rows
+    if frames == 2:
+        k, v = (torch.randn(1, 3, 1, 35, 128, device="cuda").bfloat16() for _ in range(2))
+        v[0, 0, 0, 34, 7] = float("inf")
+        pair.gpu.append_frame([0], k, v)
+        pair.gpu.synthesize(0)
+        o, _ = pair.gpu.attend(0, qd * 0.01)
+        torch.cuda.synchronize()
+        inf = torch.isinf(o)
+        assert bool(inf[0, :, 0, 7].all()) and int(inf.sum()) == tq and not bool(torch.isnan(o).any())
