@@ -22,10 +22,10 @@ constexpr int F32_KEYS = 32;    // keys per tile of the float32 readout
 constexpr int NUM_SIMD = 1024;  // 256 compute units of four SIMDs
 constexpr int KMAX = 65535;     // prototype slots per unit (slot ids fit 16 bits)
 constexpr int PCW = SMAX + 2;   // words per (slot, K/V) decode record: S tuples, no-residual flag, tau (key record) / n (value record)
-// The bf16 readout forms pseudo-token rows in LDS from at most PS_SLOTS slots
-// per 64-row tile, which holds for S >= PS_MIN_S (64 consecutive rows span
-// floor(63 / S) + 2 slots at most); below that the synthesis writes the rows.
-constexpr int PS_SLOTS = 14;
+// The bf16 readout forms pseudo-token rows in LDS from whole slots, 64 / S <=
+// PS_SLOTS of them per 64-row tile for S >= PS_MIN_S; below that the synthesis
+// writes the rows.
+constexpr int PS_SLOTS = 12;
 constexpr int PS_MIN_S = 5;
 constexpr int MT_KMAX = 2048;   // largest capacity the maintenance pass supports (its LDS)
 constexpr int AL_KMAX = 4096;   // largest capacity of the variance-aware allocation (its LDS)
@@ -171,7 +171,7 @@ struct AttendArgs {
   int splits;       // context splits per kv head
   int chunk;        // context tokens per split (multiple of 64; rows written, gen 0)
   int near_chunk;   // gen 1: near-window tokens per split (multiple of 64) ...
-  int far_chunk;    // ... and pseudo-token rows per split (multiple of 64)
+  int far_slots;    // ... and pseudo-token slots per split (multiple of the 64 / S of a tile)
   int gen;          // bf16: pseudo-token rows are formed from centres, codes and codebooks (else read from pk, pv)
   const uint8_t* near_k;  // near-window keys: ring_k, or ring_kr with rotary positions
   const float* rowbias;   // bias per pseudo-token row [units][K*S] (variance-aware allocation), else null

@@ -660,9 +660,10 @@ static protokv_status plan_attend(protokv_t h, int32_t sid, const void* q, int32
     // share of the near-window tiles and of the formed tiles, which cost
     // more than the tiles loaded directly
     aa.near_chunk = std::max(64, up64((aa.n_near + splits - 1) / splits));
-    aa.far_chunk = std::max(64, up64((aa.n_far + splits - 1) / splits));
+    const int nact = h->synth_active, nsl = 64 / h->dm.S;
+    aa.far_slots = std::max(nsl, ((nact + splits - 1) / splits + nsl - 1) / nsl * nsl);
     aa.splits = std::max((aa.n_near + aa.near_chunk - 1) / aa.near_chunk,
-                         (aa.n_far + aa.far_chunk - 1) / aa.far_chunk);
+                         (nact + aa.far_slots - 1) / aa.far_slots);
     aa.chunk = 0;
     return PROTOKV_OK;
   }

@@ -1452,6 +1452,7 @@ __device__ __forceinline__ void lds_barrier() {
   __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
   asm volatile("s_barrier" ::: "memory");
 }
+constexpr int A32_CW = 80;        // bytes from codeword to codeword in LDS (16 of padding: 16 of them on 16 different bank quads)
 constexpr int AT_NBUF = 4;        // tile buffers: tile t computes while t+1..t+3 load
 constexpr int AT_NTAB = 5;        // row-table entries (written 3 tiles ahead)
 constexpr int AT_PB_MAX = 2048;   // pseudo-token biases staged in LDS up to this capacity
@@ -1737,62 +1738,52 @@ __global__ __launch_bounds__(NW * 64, 1) void k_attend_bf16(Dims dm, Workspace w
 
   // Pseudo-token tiles formed in LDS (aa.gen): row (k, s) of K is
   // bf16(c_k + concat_g C^K_g[z_{s,g}]) (c_k alone when the slot has no
-  // residual), the values k_materialize writes; likewise V.  The inputs of a
-  // tile (the bank rows' float32 sums, 1 KiB per slot, and decode records of
-  // its <= PS_SLOTS slots) go by DMA into one of three 16 KiB staging buffers
-  // three tiles ahead, with PS_INSTR load instructions per tile spread evenly
-  // over the waves (unused ones repeat a valid slot), so every wave's
-  // outstanding count is known; two tiles ahead the sums are turned into
-  // centres in place.  Iteration t: wait for tile t+2's inputs, barrier,
-  // issue tile t+3's, convert tile t+2's, form tile t+1 into buffer
-  // (t+1) % 2, compute tile t: the forming of the next tile overlaps the
-  // MFMA work of the current one.
-  // LDS: buffers 0, 1 the formed tiles, s_kv[2][0] the unit's codebooks (16
-  // KiB), s_kv[2][1] .. s_kv[3][1] the staging buffers.
-  const int ps0 = min(aa.n_far, split * aa.far_chunk), ps1 = min(aa.n_far, ps0 + aa.far_chunk);
-  const int npt = aa.gen && ps1 > ps0 ? (ps1 - ps0 + AT_KEYS - 1) / AT_KEYS : 0;
+  // residual), the values k_materialize writes; likewise V.  A tile is 64 / S
+  // whole slots, so that a thread's row belongs to the same slot of every tile
+  // and everything it derives from its row (centre, tuple, codebook and store
+  // addresses) is computed once (tiles of 64 rows across slots, derived anew for
+  // every 16 bytes: high resolution 740 us against 614, 448 rows over K = 1024
+  // 507 against 443, 7B 95 against 89).  The inputs of a tile (the
+  // bank rows' float32 sums, 1 KiB per slot, and decode records of its slots)
+  // go by DMA into one of three staging buffers three tiles ahead; two tiles
+  // ahead the sums are turned into centres in place.  Iteration t: wait for
+  // tile t+2's inputs, barrier, issue tile t+3's, convert tile t+2's, form tile
+  // t+1 into buffer (t+1) % 2, compute tile t: the forming of the next tile
+  // overlaps the MFMA work of the current one.
+  // LDS: buffers 0, 1 the formed tiles, buffers 2 and 3 the unit's codebooks
+  // and the staging buffers.  Slots at PS_CS and codewords at A32_CW bytes from
+  // each other: lanes reading one part of different ones hit different banks.
+  const int nsl = 64 / dm.S;
+  const int nact = aa.n_far / dm.S;
+  const int ks0 = min(nact, split * aa.far_slots), ks1 = min(nact, ks0 + aa.far_slots);
+  const int npt = aa.gen && ks1 > ks0 ? (ks1 - ks0 + nsl - 1) / nsl : 0;
   if (npt > 0) {  // uniform
-    constexpr int PS_INSTR = 16;                        // PS_SLOTS centre loads + 2 record loads
-    constexpr int PS_STAGE = AT_TILE_BYTES;             // 16 KiB
-    constexpr int PS_REC = PS_SLOTS * 1024;             // records at this offset of a stage
-    constexpr int IPW = PS_INSTR / NW;                  // load instructions per wave per tile
-    constexpr int CPT = 2 * AT_KEYS * 16 / (NW * 64);   // 16-byte chunks formed per thread per tile
-    static_assert(PS_REC + 2 * 1024 <= PS_STAGE && 2 * PCW * 4 * PS_SLOTS <= 2 * 1024, "stage layout");
-    static_assert(1024 % (NW * 64) == 0, "a thread's chunks of one pass are all K or all V");
+    constexpr int PS_CS = 1024 + 32;                    // bytes of one slot's centres, K then V (32 of padding)
+    constexpr int PS_REC = PS_SLOTS * PS_CS;            // records at this offset of a stage
+    constexpr int PS_STAGE = PS_REC + 2 * 1024;
+    constexpr int CB_BYTES = 2 * G * CMAX * A32_CW;
+    static_assert(NW == 8, "a thread forms one row's chunks c and c + 8 of K and of V");
+    static_assert(2 * PCW * 4 * PS_SLOTS <= 2 * 1024 && CB_BYTES + 3 * PS_STAGE <= 4 * AT_TILE_BYTES, "LDS layout");
+    static_assert(CB_BYTES % 1024 == 0 && PS_STAGE % 16 == 0, "DMA of whole KiB to 16-byte places");
     const int S = dm.S;
-    const float invS2 = 1.0f / (float)S;
-    auto divS = [&](int x) {
-      int k = (int)((float)x * invS2);
-      k -= k * S > x ? 1 : 0;
-      k += (k + 1) * S <= x ? 1 : 0;
-      return k;
-    };
     uint8_t* s_cbb = s_kv[2][0];
-    uint8_t* s_stage = s_kv[2][1];
+    uint8_t* s_stage = s_cbb + CB_BYTES;
     const size_t ubase = (size_t)u * dm.K;
-    // Staged centre of the slot at stage position i: 16-byte unit (K/V half
-    // kvh, part 2 cl + e) at kvh * 32 + (2 cl + e + 2 i) % 32, so that rows of
-    // different slots reading one chunk fall on different banks.
     auto stage = [&](int t) {
-      const int r0 = ps0 + t * AT_KEYS;
-      const int kA = divS(r0), kB = divS(min(r0 + AT_KEYS, ps1) - 1);
-      const int nk = kB - kA + 1;
+      const int k0 = ks0 + t * nsl, nk = min(nsl, ks1 - k0);
       uint8_t* sb = s_stage + (t % 3) * PS_STAGE;
 #pragma unroll
-      for (int q = 0; q < IPW; ++q) {
-        const int i = wave + q * NW;  // uniform
-        const uint8_t* src;
-        uint8_t* dst;
-        if (i < PS_SLOTS) {
-          const int part = (lane & 32) + (((lane & 31) - 2 * i) & 31);
-          src = ws.bank + (unit * dm.K + kA + min(i, nk - 1)) * ROW + ROW_SUMK + part * 16;
-          dst = sb + i * 1024;
-        } else {
+      for (int q = 0; q < 2; ++q) {
+        const int i = wave + q * NW;  // uniform: 0 .. PS_SLOTS - 1 sums, then two of records
+        if (i < nsl) {
+          // slots past the split's last repeat it
+          lds_dma16(ws.bank + (unit * dm.K + k0 + min(i, nk - 1)) * ROW + ROW_SUMK + lane * 16, sb + i * PS_CS);
+        } else if (i >= PS_SLOTS && i < PS_SLOTS + 2) {
+          // past the last slot: its last 16 bytes (n in their last word)
           const int ch = min((i - PS_SLOTS) * 64 + lane, nk * (2 * PCW / 4) - 1);
-          src = reinterpret_cast<const uint8_t*>(ws.pcodes + (ubase + kA) * 2 * PCW) + ch * 16;
-          dst = sb + PS_REC + (i - PS_SLOTS) * 1024;
+          lds_dma16(reinterpret_cast<const uint8_t*>(ws.pcodes + (ubase + k0) * 2 * PCW) + ch * 16,
+                    sb + PS_REC + (i - PS_SLOTS) * 1024);
         }
-        lds_dma16(src, dst);
       }
     };
     // The staged sums of tile t's slots become their float32 centres
@@ -1800,147 +1791,135 @@ __global__ __launch_bounds__(NW * 64, 1) void k_attend_bf16(Dims dm, Workspace w
     // from the staged value records.
     const bool ema = (dm.flags & PROTOKV_FLAG_EMA_CENTRES) != 0;
     auto convert = [&](int t) {
-      const int r0 = ps0 + t * AT_KEYS;
-      const int kA = divS(r0), kB = divS(min(r0 + AT_KEYS, ps1) - 1);
-      const int nk = kB - kA + 1;
+      const int nk = min(nsl, ks1 - ks0 - t * nsl);
       uint8_t* sb = s_stage + (t % 3) * PS_STAGE;
       const uint32_t* recs = reinterpret_cast<const uint32_t*>(sb + PS_REC);
-      for (int x = tid; x < nk * 64; x += NW * 64) {
-        const int i = x >> 6;
-        float4* c4 = reinterpret_cast<float4*>(sb + i * 1024) + (x & 63);
-        const float nf = ema ? 1.f : (float)recs[(i * 2 + 1) * PCW + SMAX + 1];
+      if (ema) return;
+      for (int i = wave; i < nk; i += NW) {  // uniform
+        float4* c4 = reinterpret_cast<float4*>(sb + i * PS_CS) + lane;
+        const float nf = (float)recs[(i * 2 + 1) * PCW + SMAX + 1];
         const float4 v = *c4;
         *c4 = make_float4(v.x / nf, v.y / nf, v.z / nf, v.w / nf);
       }
     };
     // Tile t from stage t % 3 into buffer t % 2, in the layouts of the near
-    // tiles.  A thread forms the 16-byte store units q = tid + e * NW * 64 of
-    // K (row q % 64, chunk q / 64) and of V (row q / 4 % 64, chunk
-    // 4 (q / 256) + q % 4): one K row and one V row per thread, and each
-    // store instruction writes 1 KiB contiguous.  The K chunks of a thread
-    // come in rotate-half pairs (chunk c and c + 8 hold dims i and i + D/2),
-    // so with rotary positions each formed key, rounded to bf16 as written,
-    // is turned at tau_k in registers (float32, the roundings of
-    // k_materialize16) and rounded again.
+    // tiles: a thread forms K row tid % 64, chunks tid / 64 and + 8 (dims i
+    // and i + D / 2: with rotary positions each key, rounded to bf16 as
+    // written, is turned at tau_k in registers, with the roundings of
+    // k_materialize16, and rounded again), and V row tid / 4 % 64, chunks
+    // 4 (tid / 256) + tid % 4 and + 8: each store instruction writes 1 KiB
+    // contiguous per wave.
     const bool rope = ws.rope_inv != nullptr;  // uniform
+    struct Mine {
+      int row, j, cen, tup, flag, cw, shift;  // byte offsets in a stage and in the codebooks
+    } mine[2];
+#pragma unroll
+    for (int kv = 0; kv < 2; ++kv) {
+      const int row = kv ? (tid >> 2) & 63 : tid & 63;
+      const int chunk = kv ? 4 * (tid >> 8) + (tid & 3) : tid >> 6;
+      const int j = min(row / S, nsl - 1), s2 = min(row - j * S, S - 1), g = chunk >> 1;
+      mine[kv].row = row;
+      mine[kv].j = j;
+      mine[kv].cen = j * PS_CS + kv * 512 + chunk * 32;
+      mine[kv].tup = PS_REC + ((j * 2 + kv) * PCW + s2) * 4;
+      mine[kv].flag = PS_REC + ((j * 2 + kv) * PCW + SMAX) * 4;
+      mine[kv].cw = (kv * G + g) * CMAX * A32_CW + (chunk & 1) * 32;
+      mine[kv].shift = 4 * (G - 1 - g);
+    }
     auto form = [&](int t) {
-      constexpr int UPT = 1024 / (NW * 64);  // units per thread of K (and of V)
-      const int r0 = ps0 + t * AT_KEYS;
-      const int kA = divS(r0);
+      const int k0 = ks0 + t * nsl;
       const uint8_t* sb = s_stage + (t % 3) * PS_STAGE;
       const int pb = t & 1;
-      // the 8 values c + m w of 16-byte unit q (chunk cl) of the row of slot
-      // j, tuple tup, as float
-      auto unit8 = [&](int kv, int q, int cl, int j, uint32_t tup, float m, const float4* cen, float (&x)[8]) {
-        const float4 ca = cen[(2 * cl + 2 * j) & 31], cb = cen[(2 * cl + 1 + 2 * j) & 31];
-        const int g = cl >> 1;
-        const int z = (tup >> (4 * (G - 1 - g))) & 15;
-        const float4* cw = reinterpret_cast<const float4*>(s_cbb) + ((kv * G + g) * CMAX + z) * 4;
-        const int zr = z >> 2;
-        const float4 wa = cw[(2 * (cl & 1) + zr) & 3], wb = cw[(2 * (cl & 1) + 1 + zr) & 3];
-        // w * m + c is exactly c + w (m = 1) or c (m = 0)
+      const bool tail = nsl * S < 64 || k0 + nsl > ks1;  // uniform: rows past the tile's slots
+      // 8 values at centre c, codeword w: exactly c + w or (m 0) c
+      auto values = [](const uint8_t* c, const uint8_t* w, float m, float (&x)[8]) {
+        const float4 ca = reinterpret_cast<const float4*>(c)[0], cb = reinterpret_cast<const float4*>(c)[1];
+        const float4 wa = reinterpret_cast<const float4*>(w)[0], wb = reinterpret_cast<const float4*>(w)[1];
         x[0] = fmaf(wa.x, m, ca.x); x[1] = fmaf(wa.y, m, ca.y); x[2] = fmaf(wa.z, m, ca.z); x[3] = fmaf(wa.w, m, ca.w);
         x[4] = fmaf(wb.x, m, cb.x); x[5] = fmaf(wb.y, m, cb.y); x[6] = fmaf(wb.z, m, cb.z); x[7] = fmaf(wb.w, m, cb.w);
       };
-      auto store8 = [&](int kv, int q, const float (&x)[8]) {
+      auto store8 = [&](int kv, int e, const float (&x)[8]) {
         const bf16x2 o0 = {(__bf16)x[0], (__bf16)x[1]}, o1 = {(__bf16)x[2], (__bf16)x[3]};
         const bf16x2 o2 = {(__bf16)x[4], (__bf16)x[5]}, o3 = {(__bf16)x[6], (__bf16)x[7]};
-        *reinterpret_cast<uint4*>(s_kv[pb][kv] + q * 16) =
+        *reinterpret_cast<uint4*>(s_kv[pb][kv] + (tid + e * 512) * 16) =
             make_uint4(__builtin_bit_cast(uint32_t, o0), __builtin_bit_cast(uint32_t, o1),
                        __builtin_bit_cast(uint32_t, o2), __builtin_bit_cast(uint32_t, o3));
       };
 #pragma unroll
       for (int kv = 0; kv < 2; ++kv) {
-        const int row = kv ? (tid >> 2) & 63 : tid & 63;
-        const bool valid = r0 + row < ps1;
-        const int prow = valid ? r0 + row : r0;  // rows past the context repeat a valid row (bias -inf)
-        const int k = divS(prow);
-        const int j = k - kA, s2 = prow - k * S;
-        const uint32_t* rec = reinterpret_cast<const uint32_t*>(sb + PS_REC) + (j * 2 + kv) * PCW;
-        const uint32_t tup = rec[s2];
-        const float m = rec[SMAX] != 0u ? 0.f : 1.f;  // no residual: the centre alone
-        const float4* cen = reinterpret_cast<const float4*>(sb + j * 1024 + kv * 512);
+        const Mine& mn = mine[kv];
+        const uint32_t tup = *reinterpret_cast<const uint32_t*>(sb + mn.tup) >> mn.shift;  // chunk's nibble lowest
+        const uint32_t tup8 = *reinterpret_cast<const uint32_t*>(sb + mn.tup) >> (mn.shift - 16);  // chunk + 8's
+        const float m = *reinterpret_cast<const uint32_t*>(sb + mn.flag) != 0u ? 0.f : 1.f;  // no residual: the centre alone
+        float xl[8], xh[8];
+        values(sb + mn.cen, s_cbb + mn.cw + (tup & 15) * A32_CW, m, xl);
+        values(sb + mn.cen + 256, s_cbb + mn.cw + 4 * CMAX * A32_CW + (tup8 & 15) * A32_CW, m, xh);
+        const bool ok = mn.row < nsl * S && k0 + mn.j < ks1;
         if (kv == 0 && rope) {
-          // K units e and e + UPT/2: chunks cl < 8 and cl + 8
+          const float4* cs = reinterpret_cast<const float4*>(&s_rtab[pb][mn.j][8 * (tid >> 6)]);
 #pragma unroll
-          for (int e = 0; e < UPT / 2; ++e) {
-            const int ql = tid + e * NW * 64, qh = ql + (UPT / 2) * NW * 64;
-            const int cl = ql >> 6;
-            float xl[8], xh[8];
-            unit8(0, ql, cl, j, tup, m, cen, xl);
-            unit8(0, qh, cl + 8, j, tup, m, cen, xh);
-            const float4* cs = reinterpret_cast<const float4*>(&s_rtab[pb][j][8 * cl]);
+          for (int i2 = 0; i2 < 4; ++i2) {
+            const float4 a = cs[i2];  // (cos, sin) of two pair indices
 #pragma unroll
-            for (int i2 = 0; i2 < 4; ++i2) {
-              const float4 a = cs[i2];  // (cos, sin) of pair indices 8 cl + 2 i2, + 1
-#pragma unroll
-              for (int h = 0; h < 2; ++h) {
-                const int i = 2 * i2 + h;
-                const float c = h ? a.z : a.x, sn = h ? a.w : a.y;
-                const float x1 = (float)(__bf16)xl[i], x2 = (float)(__bf16)xh[i];
-                float lo, hi;
-                rope_pair(x1, x2, c, sn, lo, hi);
-                xl[i] = lo;
-                xh[i] = hi;
-              }
+            for (int h = 0; h < 2; ++h) {
+              const int i = 2 * i2 + h;
+              const float c = h ? a.z : a.x, sn = h ? a.w : a.y;
+              const float x1 = (float)(__bf16)xl[i], x2 = (float)(__bf16)xh[i];
+              float lo, hi;
+              rope_pair(x1, x2, c, sn, lo, hi);
+              xl[i] = lo;
+              xh[i] = hi;
             }
-            store8(0, ql, xl);
-            store8(0, qh, xh);
-          }
-        } else {
-#pragma unroll
-          for (int e = 0; e < UPT; ++e) {
-            const int q = tid + e * NW * 64;
-            const int cl = kv ? (q >> 8) * 4 + (q & 3) : q >> 6;
-            float x[8];
-            unit8(kv, q, cl, j, tup, m, cen, x);
-            store8(kv, q, x);
           }
         }
-        if (kv == 0 && tid < AT_KEYS)  // row == tid
-          s_bias[pb][row] = valid ? (pb_lds ? s_pb[k] : ws.pbias[ubase + k] * LOG2E) : -INFINITY;
+        if (kv == 1 && tail) {  // weight 0, but 0 x inf would not be 0
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            xl[i] = ok ? xl[i] : 0.f;
+            xh[i] = ok ? xh[i] : 0.f;
+          }
+        }
+        store8(kv, 0, xl);
+        store8(kv, 1, xh);
+        if (kv == 0 && tid < AT_KEYS) {  // row == tid
+          const int k = min(k0 + mn.j, ks1 - 1);
+          s_bias[pb][tid] = ok ? (pb_lds ? s_pb[k] : ws.pbias[ubase + k] * LOG2E) : -INFINITY;
+        }
       }
     };
     // (cos, sin) table of tile t's slots from tau_k in the staged key
-    // records (stage t % 3), into table t % 2: a thread's pair index i =
-    // tid % 64 is the same for every entry it computes
-    const double rinv = rope ? ws.rope_inv[tid & 63] : 0.0;
+    // records (stage t % 3), into table t % 2: lane = pair index
+    const double rinv = rope ? ws.rope_inv[lane] : 0.0;
     auto rtab = [&](int t) {
-      const int r0 = ps0 + t * AT_KEYS;
-      const int kA = divS(r0), kB = divS(min(r0 + AT_KEYS, ps1) - 1);
-      const int nk = kB - kA + 1;
+      const int nk = min(nsl, ks1 - ks0 - t * nsl);
       const uint32_t* recs = reinterpret_cast<const uint32_t*>(s_stage + (t % 3) * PS_STAGE + PS_REC);
-      for (int x = tid; x < nk * 64; x += NW * 64) {
-        const int jj = x >> 6;
-        const double tau = (double)(int32_t)recs[jj * 2 * PCW + SMAX + 1];
+      for (int i = wave; i < nk; i += NW) {  // uniform
+        const double tau = (double)(int32_t)recs[i * 2 * PCW + SMAX + 1];
         float c, sn;
         rope_cs(tau, rinv, c, sn);
-        s_rtab[t & 1][jj][tid & 63] = make_float2(c, sn);
+        s_rtab[t & 1][i][lane] = make_float2(c, sn);
       }
     };
 
     lds_barrier();  // every wave is done with the near tiles (buffers and bias entries are reused)
-    // codebooks as [K/V][subspace][codeword][4 parts of 16 bytes], part s of
-    // codeword z at position (s + z / 4) % 4: rows reading one chunk of
-    // different codewords fall on different banks
+    // codebooks [K/V][subspace][codeword] at A32_CW: 16-byte unit x is part
+    // x % 5 of codeword x / 5 (the fifth is padding)
 #pragma unroll
-    for (int q = 0; q < 16 / NW; ++q) {
-      const int i = wave + q * NW;
-      const int pos = i * 64 + lane;
-      const int z = (pos >> 2) & 15;
-      const int part = (pos & ~3) + (((pos & 3) - (z >> 2)) & 3);
-      lds_dma16(reinterpret_cast<const uint8_t*>(ws.codebooks + unit * (2 * G * CMAX * DP)) + part * 16,
-                s_cbb + i * 1024);
+    for (int q = 0; q < (CB_BYTES / 1024 + NW - 1) / NW; ++q) {
+      const int i = wave + q * NW;  // uniform
+      if (i < CB_BYTES / 1024) {
+        const int x = i * 64 + lane, z = x / 5;
+        lds_dma16(reinterpret_cast<const uint8_t*>(ws.codebooks + unit * (2 * G * CMAX * DP)) + z * 64 + min(x - 5 * z, 3) * 16,
+                  s_cbb + i * 1024);
+      }
     }
     stage(0);
     if (npt > 1) stage(1);
-    if (npt > 2) stage(2);
-    // codebooks and tiles 0 and 1's inputs have landed (tile 2's may be in
-    // flight): both are converted (and with rotary positions get their
-    // tables) before tile 0 is formed
-    if (npt > 2) wait_vm<IPW>();
-    else wait_vm<0>();
+    // codebooks and tiles 0 and 1's inputs have landed: both are converted
+    // (and with rotary positions get their tables) before tile 0 is formed
+    wait_vm<0>();
     lds_barrier();
+    if (npt > 2) stage(2);
     convert(0);
     if (npt > 1) convert(1);
     if (rope) {
@@ -2048,7 +2027,6 @@ constexpr int A32_W = 8;                       // waves per workgroup
 constexpr int A32_VB = 32 * 64 + 64;           // bytes of one 32-dim block of a V tile (64 of padding: bank spread)
 constexpr int A32_SLOTS = 5;                   // slots per formed tile, at most
 constexpr int A32_CS = 1024 + 64;              // bytes of one slot's centres, K then V (64 of padding)
-constexpr int A32_CW = 80;                     // bytes from codeword to codeword (16 of padding: 16 of them on 16 different bank quads)
 constexpr int A32_CEN = 4 * A32_VB;            // wave's LDS: V tile, centres, records, row biases, rotary table
 constexpr int A32_REC = A32_CEN + A32_SLOTS * A32_CS;
 constexpr int A32_BIAS = A32_REC + 768;        // 5 records of 144 bytes

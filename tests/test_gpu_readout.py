@@ -167,3 +167,29 @@ def test_few_row_readout(grp, tq, S, cap, frames, theta):
         torch.cuda.synchronize()
         inf = torch.isinf(o)
         assert bool(inf[0, :, 0, 7].all()) and int(inf.sum()) == tq and not bool(torch.isnan(o).any())
+
+
+# 40 .. 48 rows (key halves shared by wave pairs) and 136 (a wave per 32 rows); 12,
+# 9, 4 and 4 whole slots per 64-row tile (60, 63, 52 and 64 rows), last tiles short
+@pytest.mark.parametrize("grp,tq,S,cap,theta", [(4, 10, 5, 37, 0.0), (8, 17, 7, 40, 1e4), (4, 12, 13, 30, 0.0),
+                                                (8, 5, 16, 33, 1e4)])
+def test_formed_tiles_of_whole_slots(grp, tq, S, cap, theta):
+    """bf16 readout of more than 32 query rows per kv head, pseudo-token tiles of
+    whole slots formed in LDS and then rows written, against the oracle."""
+    import torch
+    h = H()
+    wl = W.WORKLOADS["7b"].with_(num_layers=2, num_kv_heads=1, num_q_heads=grp, grid_h=7, grid_w=7, frames=12,
+                                 window_frames=3, capacity=cap, query_tokens=tq)
+    h.log(f"case: formed tiles rows {grp * tq} S={S} K={cap} theta {theta}")
+    pair = _stream(h, wl, S=S, B=max(32, S), rope_theta=theta)
+    q = pair.query(np.random.default_rng(S))
+    oo, ol = pair.oracle[0].attend(q, wl.num_kv_heads, pair.oracle[0].synthesize())
+    qd = torch.from_numpy(q).to("cuda", torch.bfloat16).contiguous()
+    pair.gpu.synthesize(0)
+    for form in ("formed", "written"):
+        o, lse = pair.gpu.attend(0, qd)
+        torch.cuda.synchronize()
+        err, el = np.abs(o.float().cpu().numpy() - oo).max(), np.abs(lse.cpu().numpy() - ol).max()
+        h.log(f"{form} rows: err {err:.2e}, lse {el:.2e}")
+        assert err <= h.READOUT_ATOL and el <= h.LSE_ATOL
+        pair.gpu.read_pseudo()   # writes the rows
