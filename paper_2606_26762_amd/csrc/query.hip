@@ -1418,6 +1418,7 @@ hipError_t launch_materialize(const Dims& dm, const Workspace& ws, int sid, int 
 // ---------------------------------------------------------------------------
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
+constexpr float SQRT_D = 11.313708498984761f;  // a logit in units of q.k
 
 // bf16 path.  Workgroup = eight waves for one (kv head, context split,
 // block of query rows): one wave per 32 rows for up to 256 rows (KH = 1), or
@@ -1462,9 +1463,9 @@ __global__ __launch_bounds__(NW * 64, 1) void k_attend_bf16(Dims dm, Workspace w
   constexpr int LPT = 32 / NW;  // load instructions per wave per tile
   constexpr int RPW = NW * 32 / KH;  // query rows per workgroup
   __shared__ __attribute__((aligned(16))) uint8_t s_kv[AT_NBUF][2][AT_TILE_BYTES];   // [buffer][K,V]
-  __shared__ __attribute__((aligned(16))) float s_bias[AT_NTAB][AT_KEYS];           // log2(e) * bias, -inf past the context
+  __shared__ __attribute__((aligned(16))) float s_bias[AT_NTAB][AT_KEYS];           // bias in units of q.k, -inf past the context
   __shared__ const uint8_t* s_rowp[AT_NTAB][2][AT_KEYS];                             // K and V address of each tile row
-  __shared__ float s_pb[AT_PB_MAX];                                                  // log2(e) * ln n_k of this unit
+  __shared__ float s_pb[AT_PB_MAX];                                                  // ln n_k of this unit in units of q.k
   // rotary positions: (cos, sin) of tau_k * theta^(-2i/D) for the slots of
   // a formed tile, two tiles' tables (the next one's is written ahead)
   __shared__ float2 s_rtab[2][PS_SLOTS][D / 2];
@@ -1490,7 +1491,7 @@ __global__ __launch_bounds__(NW * 64, 1) void k_attend_bf16(Dims dm, Workspace w
   const int ntiles = c1n > c0 ? (c1n - c0 + AT_KEYS - 1) / AT_KEYS : 0;
   const bool pb_lds = dm.K <= AT_PB_MAX;
   if (pb_lds)
-    for (int k = tid; k < dm.K; k += NW * 64) s_pb[k] = ws.pbias[(size_t)u * dm.K + k] * LOG2E;
+    for (int k = tid; k < dm.K; k += NW * 64) s_pb[k] = ws.pbias[(size_t)u * dm.K + k] * SQRT_D;
 
   const int col = lane & 31, half = lane >> 5;
   // KH = 2: waves w and w + NW / 2 take the same 32 query rows and the two
@@ -1533,12 +1534,12 @@ __global__ __launch_bounds__(NW * 64, 1) void k_attend_bf16(Dims dm, Workspace w
       kp = ws.pk + off;
       vp = ws.pv + off;
       if (aa.rowbias) {
-        if (idx < c1n) bv = aa.rowbias[(size_t)u * dm.K * dm.S + prow] * LOG2E;
+        if (idx < c1n) bv = aa.rowbias[(size_t)u * dm.K * dm.S + prow] * SQRT_D;
       } else {
         int k = (int)((float)prow * invS);
         k -= k * dm.S > prow ? 1 : 0;
         k += (k + 1) * dm.S <= prow ? 1 : 0;
-        if (idx < c1n) bv = pb_lds ? s_pb[k] : ws.pbias[(size_t)u * dm.K + k] * LOG2E;
+        if (idx < c1n) bv = pb_lds ? s_pb[k] : ws.pbias[(size_t)u * dm.K + k] * SQRT_D;
       }
     }
   };
@@ -1586,10 +1587,10 @@ __global__ __launch_bounds__(NW * 64, 1) void k_attend_bf16(Dims dm, Workspace w
   const int voff = (4 * half + (s16 >> 2)) * 64 + (grp16 & 1) * 32 + (s16 & 3) * 8;
   const bf16x2 ones2 = {(__bf16)1.0f, (__bf16)1.0f};
 
-  // one 64-key tile in LDS (K at kt, V at vt): S^T = K Q^T, scores with the
-  // tile's biases, online softmax, O^T += V^T P.  Without BIAS (a full tile of
-  // near-window keys after the first tile, all biases 0) the scores are taken
-  // relative to the running reference in the same multiply-add.
+  // one 64-key tile in LDS (K at kt, V at vt): S^T = K Q^T, online softmax,
+  // O^T += V^T P.  BIAS: the products start from the keys' biases (the tile's
+  // bias entries, in units of q.k); a full tile of near-window keys starts
+  // from 0.
   auto compute_tile = [&](const uint8_t* kt, const uint8_t* vt, int tb, auto bias_tag) {
     constexpr bool BIAS = decltype(bias_tag)::value;
     const uint8_t* kl = kt + koff;
@@ -1601,78 +1602,65 @@ __global__ __launch_bounds__(NW * 64, 1) void k_attend_bf16(Dims dm, Workspace w
     for (int hh = 0; hh < NH; ++hh) {
       const int h = KH == 2 ? kh : hh;
       sacc[hh] = (f32x16){0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      if constexpr (BIAS) {
+        // element i is key h * 32 + (i / 4) * 8 + half * 4 + i % 4
+  #pragma unroll
+        for (int i4 = 0; i4 < 4; ++i4) {
+          const float4 bb = *reinterpret_cast<const float4*>(&s_bias[tb][h * 32 + i4 * 8 + half * 4]);
+          sacc[hh][i4 * 4] = bb.x;
+          sacc[hh][i4 * 4 + 1] = bb.y;
+          sacc[hh][i4 * 4 + 2] = bb.z;
+          sacc[hh][i4 * 4 + 3] = bb.w;
+        }
+      }
   #pragma unroll
       for (int kk = 0; kk < 8; ++kk) {
         const bf16x8 ak = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8*>(kl + kk * 2048 + h * 512));
         sacc[hh] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ak, bq[kk], sacc[hh], 0, 0, 0);
       }
     }
-    // scores x = s * scale + bias (key m = h*32 + (i/4)*8 + half*4 + i%4),
-    // without BIAS x = s * scale - mref
+    // V operands read before the softmax (their LDS latency under its
+    // arithmetic): all of a half tile's, or the first of four 32-dim blocks
+    constexpr int VP = KH == 2 ? 4 : 1;
+    v8i16 va[4][2 * NH];
+    auto read_v = [&](int b) {
+  #pragma unroll
+      for (int st = 0; st < 2 * NH; ++st) {
+        const int sk = KH == 2 ? 2 * kh + st : st;  // 16-key step of the tile
+        const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(vl + b * 4096 + sk * 1024));
+        const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(vl + b * 4096 + sk * 1024 + 512));
+        va[b][st] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      }
+    };
+  #pragma unroll
+    for (int b = 0; b < VP; ++b) read_v(b);
+    __builtin_amdgcn_sched_barrier(0);
     float tmax = -1e30f;
-    if constexpr (BIAS) {
   #pragma unroll
-      for (int hh = 0; hh < NH; ++hh) {
-        const int h = KH == 2 ? kh : hh;
+    for (int hh = 0; hh < NH; ++hh)
   #pragma unroll
-        for (int i4 = 0; i4 < 4; ++i4) {
-          const float4 bb = *reinterpret_cast<const float4*>(&s_bias[tb][h * 32 + i4 * 8 + half * 4]);
-          const float bv[4] = {bb.x, bb.y, bb.z, bb.w};
-  #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float x = fmaf(sacc[hh][i4 * 4 + e], scale, bv[e]);
-            sacc[hh][i4 * 4 + e] = x;
-            tmax = fmaxf(tmax, x);
-          }
-        }
-      }
-    } else {
-      const float nm = -mref;
-  #pragma unroll
-      for (int hh = 0; hh < NH; ++hh)
-  #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const float x = fmaf(sacc[hh][i], scale, nm);
-          sacc[hh][i] = x;
-          tmax = fmaxf(tmax, x);
-        }
-    }
-    tmax = fmaxf(tmax, xor32(tmax));
+      for (int i = 0; i < 16; ++i) tmax = fmaxf(tmax, sacc[hh][i]);
+    tmax = fmaxf(tmax, xor32(tmax)) * scale;
     // the reference moves up only when a row's max exceeds it by more than 8
-    const bool grow = BIAS ? tmax > mref + 8.0f : tmax > 8.0f;
+    const bool grow = tmax > mref + 8.0f;
     if (__ballot(grow)) {  // uniform
-      if constexpr (BIAS) {
-        const float mnew = grow ? tmax : mref;
-        const float alpha = __builtin_amdgcn_exp2f(mref - mnew);
-        lrun *= alpha;
+      const float mnew = grow ? tmax : mref;
+      const float alpha = __builtin_amdgcn_exp2f(mref - mnew);
+      lrun *= alpha;
   #pragma unroll
-        for (int b = 0; b < 4; ++b)
+      for (int b = 0; b < 4; ++b)
   #pragma unroll
-          for (int i = 0; i < 16; ++i) oacc[b][i] *= alpha;
-        mref = mnew;
-      } else {
-        const float mnew = grow ? mref + tmax : mref;
-        const float delta = mnew - mref;
-        const float alpha = __builtin_amdgcn_exp2f(-delta);
-        lrun *= alpha;
-  #pragma unroll
-        for (int b = 0; b < 4; ++b)
-  #pragma unroll
-          for (int i = 0; i < 16; ++i) oacc[b][i] *= alpha;
-  #pragma unroll
-        for (int hh = 0; hh < NH; ++hh)
-  #pragma unroll
-          for (int i = 0; i < 16; ++i) sacc[hh][i] -= delta;
-        mref = mnew;
-      }
+        for (int i = 0; i < 16; ++i) oacc[b][i] *= alpha;
+      mref = mnew;
     }
+    const float nm = -mref;
     // P in bf16; the row sum is taken over the rounded values the products use
     bf16x8 pb[2 * NH];
   #pragma unroll
     for (int hh = 0; hh < NH; ++hh)
   #pragma unroll
       for (int i = 0; i < 16; ++i)
-        pb[2 * hh + (i >> 3)][i & 7] = (__bf16)__builtin_amdgcn_exp2f(BIAS ? sacc[hh][i] - mref : sacc[hh][i]);
+        pb[2 * hh + (i >> 3)][i & 7] = (__bf16)__builtin_amdgcn_exp2f(fmaf(sacc[hh][i], scale, nm));
     float sum0 = 0.f, sum1 = 0.f;
   #pragma unroll
     for (int j = 0; j < 2 * NH; ++j) {
@@ -1691,14 +1679,10 @@ __global__ __launch_bounds__(NW * 64, 1) void k_attend_bf16(Dims dm, Workspace w
     // then holds dim d0 + i of the 4 keys.
   #pragma unroll
     for (int b = 0; b < 4; ++b) {
+      if (b + VP < 4) read_v(b + VP);
   #pragma unroll
-      for (int st = 0; st < 2 * NH; ++st) {
-        const int sk = KH == 2 ? 2 * kh + st : st;  // 16-key step of the tile
-        const v4i16 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(vl + b * 4096 + sk * 1024));
-        const v4i16 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(vl + b * 4096 + sk * 1024 + 512));
-        const v8i16 a = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-        oacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), pb[st], oacc[b], 0, 0, 0);
-      }
+      for (int st = 0; st < 2 * NH; ++st)
+        oacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, va[b][st]), pb[st], oacc[b], 0, 0, 0);
     }
   };
 
@@ -1729,8 +1713,8 @@ __global__ __launch_bounds__(NW * 64, 1) void k_attend_bf16(Dims dm, Workspace w
     if (t + 3 < ntiles) issue(t + 3);
     if (wave == 0 && t + 4 < ntiles) resolve(t + 4, nk, nv, nb);
     if (!wvalid) continue;  // uniform: a loader-only wave
-    // a full tile of near-window keys past the first has all biases 0
-    if (t > 0 && c0 + (t + 1) * AT_KEYS <= min(c1n, aa.n_near))
+    // a full tile of near-window keys has all biases 0
+    if (c0 + (t + 1) * AT_KEYS <= min(c1n, aa.n_near))
       compute_tile(s_kv[buf][0], s_kv[buf][1], tb, std::false_type{});
     else
       compute_tile(s_kv[buf][0], s_kv[buf][1], tb, std::true_type{});
@@ -1883,7 +1867,7 @@ __global__ __launch_bounds__(NW * 64, 1) void k_attend_bf16(Dims dm, Workspace w
         store8(kv, 1, xh);
         if (kv == 0 && tid < AT_KEYS) {  // row == tid
           const int k = min(k0 + mn.j, ks1 - 1);
-          s_bias[pb][tid] = ok ? (pb_lds ? s_pb[k] : ws.pbias[ubase + k] * LOG2E) : -INFINITY;
+          s_bias[pb][tid] = ok ? (pb_lds ? s_pb[k] : ws.pbias[ubase + k] * SQRT_D) : -INFINITY;
         }
       }
     };
@@ -2093,24 +2077,25 @@ __global__ __launch_bounds__(A32_W * 64, 2) void k_attend_rows32(Dims dm, Worksp
   const float4* s_bias = reinterpret_cast<const float4*>(mem + A32_BIAS);
   const bf16x2 ones2 = {(__bf16)1.0f, (__bf16)1.0f};
 
-  // softmax of the scores s (S^T of 32 keys) and O^T += V^T P from the LDS tile
-  auto weigh = [&](f32x16 s, bool biased) {
-    float tmax = -1e30f;
-    if (biased) {  // uniform
+  // the products S^T of a tile start from the keys' biases (in units of q.k)
+  auto biases = [&]() {
+    f32x16 s;
 #pragma unroll
-      for (int i4 = 0; i4 < 4; ++i4) {
-        const float4 b4 = s_bias[i4 * 2 + half];
-        const float bv[4] = {b4.x, b4.y, b4.z, b4.w};
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s[i4 * 4 + e] = fmaf(s[i4 * 4 + e], scale, bv[e]);
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < 16; ++i) s[i] *= scale;
+    for (int i4 = 0; i4 < 4; ++i4) {
+      const float4 b4 = s_bias[i4 * 2 + half];
+      s[i4 * 4] = b4.x;
+      s[i4 * 4 + 1] = b4.y;
+      s[i4 * 4 + 2] = b4.z;
+      s[i4 * 4 + 3] = b4.w;
     }
+    return s;
+  };
+  // softmax of the scores s (S^T of 32 keys) and O^T += V^T P from the LDS tile
+  auto weigh = [&](const f32x16& s) {
+    float tmax = -1e30f;
 #pragma unroll
     for (int i = 0; i < 16; ++i) tmax = fmaxf(tmax, s[i]);
-    tmax = fmaxf(tmax, xor32(tmax));
+    tmax = fmaxf(tmax, xor32(tmax)) * scale;
     const bool grow = tmax > mref + 8.0f;
     if (__ballot(grow)) {  // uniform
       const float mnew = grow ? tmax : mref;
@@ -2122,9 +2107,10 @@ __global__ __launch_bounds__(A32_W * 64, 2) void k_attend_rows32(Dims dm, Worksp
         for (int i = 0; i < 16; ++i) oacc[b][i] *= alpha;
       mref = mnew;
     }
+    const float nm = -mref;
     bf16x8 pb[2];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) pb[i >> 3][i & 7] = (__bf16)__builtin_amdgcn_exp2f(s[i] - mref);
+    for (int i = 0; i < 16; ++i) pb[i >> 3][i & 7] = (__bf16)__builtin_amdgcn_exp2f(fmaf(s[i], scale, nm));
     float sum0 = 0.f, sum1 = 0.f;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
@@ -2171,7 +2157,7 @@ __global__ __launch_bounds__(A32_W * 64, 2) void k_attend_rows32(Dims dm, Worksp
     } else {
       const int pr = pos - aa.n_near;
       row = -1 - pr;
-      bias = (aa.rowbias ? aa.rowbias[ubase * dm.S + pr] : ws.pbias[ubase + pr / dm.S]) * LOG2E;
+      bias = (aa.rowbias ? aa.rowbias[ubase * dm.S + pr] : ws.pbias[ubase + pr / dm.S]) * SQRT_D;
     }
     if (idx >= nload) bias = -INFINITY;
     return row;
@@ -2236,11 +2222,12 @@ __global__ __launch_bounds__(A32_W * 64, 2) void k_attend_rows32(Dims dm, Worksp
       }
       load_v(row, vr);
       f32x16 s = zero;
+      if (biased) s = biases();
 #pragma unroll
       for (int kk = 0; kk < 8; ++kk)
         s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kr[kk]), bq[kk], s, 0, 0, 0);
       load_k(row, kr);
-      weigh(s, biased);
+      weigh(s);
       bias = nbias;
     }
   };
@@ -2276,7 +2263,7 @@ __global__ __launch_bounds__(A32_W * 64, 2) void k_attend_rows32(Dims dm, Worksp
       }
       const bool ok = m < nsl * dm.S && ft * nsl + j < nact;  // row m is a pseudo-token
       {
-        const float b = __shfl(fb, j, 64) * LOG2E;
+        const float b = __shfl(fb, j, 64) * SQRT_D;
         if (half == 0) reinterpret_cast<float*>(mem + A32_BIAS)[m] = ok ? b : -INFINITY;
       }
       wave_lds_order();
@@ -2302,7 +2289,7 @@ __global__ __launch_bounds__(A32_W * 64, 2) void k_attend_rows32(Dims dm, Worksp
         for (int e = 0; e < 8; ++e) r[e] = (__bf16)x[e];
         return r;
       };
-      f32x16 s = zero;
+      f32x16 s = biases();
 #pragma unroll
       for (int kk = 0; kk < 4; ++kk) {
         // chunks of rotate-half pairs: dims i and i + D / 2
@@ -2338,7 +2325,7 @@ __global__ __launch_bounds__(A32_W * 64, 2) void k_attend_rows32(Dims dm, Worksp
         *reinterpret_cast<bf16x8*>(mem + (2 * half + (e >> 2)) * A32_VB + m * 64 + (e & 3) * 16) = round8(x);
       }
       wave_lds_order();
-      weigh(s, true);
+      weigh(s);
     }
   };
   // Waves w and w + 4 share a SIMD: one takes the loaded tiles first, the other the
