@@ -495,7 +495,7 @@ __device__ __forceinline__ int pq_pair(const Dims& dm, float pinf, float ninf, c
       const float d = __shfl(rex[q & 7], q < 8 ? tc : tc + 32, 64) - wc[q];
       a = a + d * d;
     }
-    if (cw >= dm.C) a = INFINITY;
+    if (cw >= dm.C || !(a < INFINITY)) a = INFINITY;  // (no distance is less: the lowest codeword)
     int ai = cw;
 #pragma unroll
     for (int o = 8; o >= 1; o >>= 1) {
@@ -1497,7 +1497,7 @@ __global__ __launch_bounds__(256, EMA ? 2 : (NP > 2 ? 3 : 4)) void k_aggregate(D
 }
 
 // ---------------------------------------------------------------------------
-// Aggregation over the touched slots only (running means, K <= AGC_KMAX).
+// Aggregation over the touched slots only (K <= AGC_KMAX).
 // A fold touches a fraction of the K slots (about 100 of 512 on a 7B-shaped
 // stream), so workgroups over fixed ranges of slots spend most of their lane
 // groups on slots without tokens.  Here each of the P workgroups of a unit
@@ -1510,11 +1510,19 @@ __global__ __launch_bounds__(256, EMA ? 2 : (NP > 2 ? 3 : 4)) void k_aggregate(D
 // flight, the row and the slot's screening copy are written back, and the
 // next touched slot's row is loaded before the current one's stores.  The
 // arithmetic is k_aggregate's: the same float32 operation sequence per slot.
+// With EMA centres the workgroup's 16 groups go on together: when a slot each
+// is absorbed and the tokens' residuals are in the workspace, the waves code
+// them as the screen does (pq_pair) and add the codes to the histograms by
+// integer atomics: 112 units x 196 tokens, K = 256, 50 -> 43 us against
+// workgroups over 32 fixed slots whose threads formed the sequential distances
+// themselves (running means 18, and the screen 12 less with EMA centres: the
+// codes' histogram lines are fetched here).  168 registers: the coding's
+// operands beside a group's row.
 // ---------------------------------------------------------------------------
 constexpr int AGC_KMAX = 4096;  // slot counters held in LDS
 
-template <int FP32>
-__global__ __launch_bounds__(256, 4) void k_aggregate_c(Dims dm, Workspace ws, FoldBatch fb, int wg_per_unit) {
+template <int FP32, int EMA>
+__global__ __launch_bounds__(256, EMA ? 3 : 4) void k_aggregate_c(Dims dm, Workspace ws, FoldBatch fb, int wg_per_unit) {
   // per slot: token count | touched flag << 16, then the exclusive prefix of
   // both (list offset | touched index << 16); entry K holds the totals
   __shared__ uint32_t s_cnt[AGC_KMAX + 1];
@@ -1601,7 +1609,9 @@ __global__ __launch_bounds__(256, 4) void k_aggregate_c(Dims dm, Workspace ws, F
   const int gi = tid >> 4, il = tid & 15;
   const int step = 16 * wg_per_unit;
   int ti = gi + 16 * wgi;
-  if (ti >= ntouched) return;  // uniform per lane group; no barrier below
+  // running means: uniform per lane group, no barrier below; EMA centres: the
+  // workgroup's groups go on together
+  if ((EMA ? 16 * wgi : ti) >= ntouched) return;
   const float eta = dm.eta, keep = 1.0f - dm.eta;
   float sk[8], sv[8], qk[8], qv[8];
   float nk[8], nv[8], nqk[8], nqv[8];
@@ -1614,77 +1624,133 @@ __global__ __launch_bounds__(256, 4) void k_aggregate_c(Dims dm, Workspace ws, F
     ld8f(row + ROW_SQV + il * 32, d);
     mm = *reinterpret_cast<const RowMeta*>(row + ROW_META);
   };
-  load_row(s_tslot[ti], sk, sv, qk, qv, m);
-  for (; ti < ntouched; ti += step) {
-    const int k = s_tslot[ti];
-    const int t0 = s_tstart[ti], t1 = s_tstart[ti + 1];
-    const size_t si = unit * K + k;
-    uint8_t* row = ws.bank + si * ROW;
-    const int tn = ti + step;
-    for (int tb = t0; tb < t1; tb += TOK_BATCH) {
-      int jb[TOK_BATCH];
-      Raw8<FP32> kb2[TOK_BATCH], vb2[TOK_BATCH];
+  if (!EMA) load_row(s_tslot[ti], sk, sv, qk, qv, m);
+  const float ak = dm.alpha, av = dm.beta, a1k = 1.0f - dm.alpha, a1v = 1.0f - dm.beta;
+  // tr: the touched slot of the first group, uniform
+  for (int tr = 16 * wgi; (EMA ? tr : ti) < ntouched; tr += step, ti += step) {
+    if (!EMA || ti < ntouched) {
+      const int k = s_tslot[ti];
+      const int t0 = s_tstart[ti], t1 = s_tstart[ti + 1];
+      const size_t si = unit * K + k;
+      uint8_t* row = ws.bank + si * ROW;
+      const int tn = ti + step;
+      if (EMA) load_row(k, sk, sv, qk, qv, m);
+      for (int tb = t0; tb < t1; tb += TOK_BATCH) {
+        int jb[TOK_BATCH];
+        Raw8<FP32> kb2[TOK_BATCH], vb2[TOK_BATCH];
 #pragma unroll
-      for (int e = 0; e < TOK_BATCH; ++e) {
-        jb[e] = s_tok[min(tb + e, t1 - 1)];
-        load8<FP32>(ws.ring_k, fbase + (size_t)jb[e] * D + 8 * il, kb2[e]);
-        load8<FP32>(ws.ring_v, fbase + (size_t)jb[e] * D + 8 * il, vb2[e]);
-      }
+        for (int e = 0; e < TOK_BATCH; ++e) {
+          jb[e] = s_tok[min(tb + e, t1 - 1)];
+          load8<FP32>(ws.ring_k, fbase + (size_t)jb[e] * D + 8 * il, kb2[e]);
+          load8<FP32>(ws.ring_v, fbase + (size_t)jb[e] * D + 8 * il, vb2[e]);
+        }
 #pragma unroll
-      for (int e = 0; e < TOK_BATCH; ++e) {
-        if (tb + e < t1) {
-          const int jj = jb[e];
+        for (int e = 0; e < TOK_BATCH; ++e) {
+          if (tb + e < t1) {
+            const int jj = jb[e];
+            if (EMA) {
+              // c <- (1 - alpha) c + alpha K, p likewise with beta; residuals
+              // against the updated centres to the workspace (coded below)
+              float rk[8], rv[8];
 #pragma unroll
-          for (int d = 0; d < 8; ++d) {
-            const float xk = raw_at<FP32>(kb2[e], d), xv = raw_at<FP32>(vb2[e], d);
-            sk[d] = sk[d] + xk;
-            sv[d] = sv[d] + xv;
-            qk[d] = qk[d] + xk * xk;
-            qv[d] = qv[d] + xv * xv;
+              for (int d = 0; d < 8; ++d) {
+                const float xk = raw_at<FP32>(kb2[e], d), xv = raw_at<FP32>(vb2[e], d);
+                sk[d] = a1k * sk[d] + ak * xk;
+                sv[d] = a1v * sv[d] + av * xv;
+                qk[d] = qk[d] + xk * xk;
+                qv[d] = qv[d] + xv * xv;
+                rk[d] = xk - sk[d];
+                rv[d] = xv - sv[d];
+              }
+              if (pq) {
+                float* rr = ws.ema_res + ((unit * N + jj) * 2) * (size_t)D + 8 * il;
+                // read back by this workgroup below: ordinary stores
+                *reinterpret_cast<float4*>(rr) = make_float4(rk[0], rk[1], rk[2], rk[3]);
+                *reinterpret_cast<float4*>(rr + 4) = make_float4(rk[4], rk[5], rk[6], rk[7]);
+                *reinterpret_cast<float4*>(rr + D) = make_float4(rv[0], rv[1], rv[2], rv[3]);
+                *reinterpret_cast<float4*>(rr + D + 4) = make_float4(rv[4], rv[5], rv[6], rv[7]);
+              }
+            } else {
+#pragma unroll
+              for (int d = 0; d < 8; ++d) {
+                const float xk = raw_at<FP32>(kb2[e], d), xv = raw_at<FP32>(vb2[e], d);
+                sk[d] = sk[d] + xk;
+                sv[d] = sv[d] + xv;
+                qk[d] = qk[d] + xk * xk;
+                qv[d] = qv[d] + xv * xv;
+              }
+            }
+            if (pq) m.n_res += 1;
+            float sx, sy;
+            token_xy(jj, dm.grid_w, dm.grid_h, sx, sy);
+            const float mx = keep * m.mu_x + eta * sx;
+            const float my = keep * m.mu_y + eta * sy;
+            m.mu_x = mx;
+            m.mu_y = my;
+            const float ddx = sx - mx, ddy = sy - my;
+            m.sxx = keep * m.sxx + eta * (ddx * ddx);
+            m.sxy = keep * m.sxy + eta * (ddx * ddy);
+            m.syy = keep * m.syy + eta * (ddy * ddy);
+            m.tau = fb.fe[b] * N + jj;
+            m.n += 1;
           }
-          if (pq) m.n_res += 1;
-          float sx, sy;
-          token_xy(jj, dm.grid_w, dm.grid_h, sx, sy);
-          const float mx = keep * m.mu_x + eta * sx;
-          const float my = keep * m.mu_y + eta * sy;
-          m.mu_x = mx;
-          m.mu_y = my;
-          const float ddx = sx - mx, ddy = sy - my;
-          m.sxx = keep * m.sxx + eta * (ddx * ddx);
-          m.sxy = keep * m.sxy + eta * (ddx * ddy);
-          m.syy = keep * m.syy + eta * (ddy * ddy);
-          m.tau = fb.fe[b] * N + jj;
-          m.n += 1;
         }
       }
-    }
-    // the next touched slot's row in flight before this one's stores
-    if (tn < ntouched) load_row(s_tslot[tn], nk, nv, nqk, nqv, nm);
-    st8f(row + ROW_SUMK + il * 32, sk);
-    st8f(row + ROW_SUMV + il * 32, sv);
-    st8f(row + ROW_SQK + il * 32, qk);
-    st8f(row + ROW_SQV + il * 32, qv);
-    // the meta and the padding after it: one whole 64-byte sector
-    if (il == 0) *reinterpret_cast<RowMeta*>(row + ROW_META) = m;
-    if (il == 1) *reinterpret_cast<RowMeta*>(row + ROW_META + sizeof(RowMeta)) = RowMeta{};
-    refresh_cache16(dm, sk, m, unit, k, ws, il);
-    if (il == 0) ws.touched[si] += 1u;
-    if (tn < ntouched) {
+      // the next touched slot's row in flight before this one's stores
+      if (!EMA && tn < ntouched) load_row(s_tslot[tn], nk, nv, nqk, nqv, nm);
+      st8f(row + ROW_SUMK + il * 32, sk);
+      st8f(row + ROW_SUMV + il * 32, sv);
+      st8f(row + ROW_SQK + il * 32, qk);
+      st8f(row + ROW_SQV + il * 32, qv);
+      // the meta and the padding after it: one whole 64-byte sector
+      if (il == 0) *reinterpret_cast<RowMeta*>(row + ROW_META) = m;
+      if (il == 1) *reinterpret_cast<RowMeta*>(row + ROW_META + sizeof(RowMeta)) = RowMeta{};
+      refresh_cache16(dm, sk, m, unit, k, ws, il);
+      if (il == 0) ws.touched[si] += 1u;
+      if (!EMA && tn < ntouched) {
 #pragma unroll
-      for (int d = 0; d < 8; ++d) {
-        sk[d] = nk[d];
-        sv[d] = nv[d];
-        qk[d] = nqk[d];
-        qv[d] = nqv[d];
+        for (int d = 0; d < 8; ++d) {
+          sk[d] = nk[d];
+          sv[d] = nv[d];
+          qk[d] = nqk[d];
+          qv[d] = nqv[d];
+        }
+        m = nm;
       }
-      m = nm;
+    }
+    if (EMA && pq) {
+      __syncthreads();  // the residuals are written
+      // the codes of these 16 slots' tokens, a wave for 32 tokens, one side
+      // and a pair of subspaces; the residuals are exact, so the bound has no
+      // centre term and the fallback subtracts 0
+      const int p0 = s_tstart[tr], np = s_tstart[min(tr + 16, ntouched)] - p0;
+      const int col = lane & 31, half = lane >> 5;
+      const float pinf = opaque(INFINITY), ninf = opaque(-INFINITY);
+      for (int job = wave; job < (np + 31) / 32 * G; job += 4) {  // uniform
+        const int p = job % (G / 2), kv = job / (G / 2) % 2, at = job / G * 32 + col;
+        const bool qv = at < np;
+        const int j = s_tok[p0 + (qv ? at : 0)];
+        const float* rr = ws.ema_res + ((unit * N + j) * 2 + kv) * (size_t)D + 2 * p * DP + half * 8;
+        const size_t ub = unit * 2 + kv;
+        const float* cbk = ws.codebooks + ub * G * CBW;
+        const float* wa = cbk + (2 * p + (col < 16 ? 0 : 1)) * CBW + (col & 15) * DP + half * 8;
+        float r[2][8], w[8];
+        const float zero[2][8] = {};
+        ld8f(reinterpret_cast<const uint8_t*>(rr), r[0]);
+        ld8f(reinterpret_cast<const uint8_t*>(rr + DP), r[1]);
+        ld8f(reinterpret_cast<const uint8_t*>(wa), w);
+        const int z = pq_pair(dm, pinf, ninf, cbk, ws.cbhn + ub * G * CMAX, ws.cbmax + ub * G, r, w, r, zero, 1.f, 0.f, 0.f,
+                              p, qv, lane);
+        uint32_t* hist = reinterpret_cast<uint32_t*>(ws.bank + (unit * K + s_asg[j]) * ROW + (kv ? ROW_HV : ROW_HK));
+        if (qv) atomicAdd(hist + (2 * p + half) * CMAX + z, 1u);
+      }
     }
   }
 }
 
 hipError_t launch_aggregate(const Dims& dm, const Workspace& ws, const FoldBatch& fb, hipStream_t st) {
   const bool ema = (dm.flags & PROTOKV_FLAG_EMA_CENTRES) != 0;
-  if (!ema && dm.K <= AGC_KMAX) {
+  if (dm.K <= AGC_KMAX) {
     // touched slots only: P workgroups per unit, enough to put about 2048
     // workgroups in flight, at most one per 16 slots a fold can touch
     const int units = fb.n * dm.units;
@@ -1692,19 +1758,20 @@ hipError_t launch_aggregate(const Dims& dm, const Workspace& ws, const FoldBatch
     const int P = std::max(1, std::min(pmax, (2048 + units - 1) / units));
     dim3 grid(units * P);
     using KFn = void (*)(Dims, Workspace, FoldBatch, int);
-    const KFn fn = dm.kv_fp32 ? k_aggregate_c<1> : k_aggregate_c<0>;
+    const KFn fn = dm.kv_fp32 ? (ema ? k_aggregate_c<1, 1> : k_aggregate_c<1, 0>)
+                              : (ema ? k_aggregate_c<0, 1> : k_aggregate_c<0, 0>);
     hipLaunchKernelGGL(fn, grid, dim3(256), 0, st, dm, ws, fb, P);
     return hipGetLastError();
   }
-  // running means: AGG_NP slots per lane group (16 AGG_NP per workgroup);
-  // EMA centres code their residuals in the workgroup: two per group
+  // more slots than the lists count in LDS: ranges of 16 AGG_NP slots per
+  // workgroup
   constexpr int NPM = AGG_NP;
-  const int slots = ema ? 32 : 16 * NPM;
+  const int slots = 16 * NPM;
   const int wpu = (dm.K + slots - 1) / slots;
   dim3 grid(fb.n * dm.units * wpu);
   using KFn = void (*)(Dims, Workspace, FoldBatch, int);
-  const KFn fn = dm.kv_fp32 ? (ema ? k_aggregate<1, 1, 2> : k_aggregate<1, 0, NPM>)
-                            : (ema ? k_aggregate<0, 1, 2> : k_aggregate<0, 0, NPM>);
+  const KFn fn = dm.kv_fp32 ? (ema ? k_aggregate<1, 1, NPM> : k_aggregate<1, 0, NPM>)
+                            : (ema ? k_aggregate<0, 1, NPM> : k_aggregate<0, 0, NPM>);
   hipLaunchKernelGGL(fn, grid, dim3(256), 0, st, dm, ws, fb, wpu);
   return hipGetLastError();
 }

@@ -311,6 +311,27 @@ def test_ema_centres(wl_name, alpha, beta):
     pair.attend(pair.query(np.random.default_rng(13)), pseudo)
 
 
+@pytest.mark.parametrize("dtype,grid,K,C,streams", [("bf16", (5, 7), 16, 12, 1), ("fp32", (17, 16), 250, 16, 1),
+                                                    ("bf16", (32, 32), 4096, 16, 1), ("bf16", (9, 9), 4097, 16, 1),
+                                                    ("fp32", (7, 9), 40, 16, 64)])
+def test_ema_centres_lists(dtype, grid, K, C, streams):
+    """EMA centres aggregated from lists of the touched slots: fewer tokens
+    than a wave, several frames of tokens per slot, the largest frame and the
+    largest capacity of that form, the first capacity of the other form, and
+    (64 streams x 32 units) one workgroup per unit, whose lane groups take
+    several slots in turn.  Banks bitwise."""
+    h = H()
+    wl = W.WORKLOADS["7b"].with_(num_layers=32 if streams > 1 else 1, num_kv_heads=1, num_q_heads=1, grid_h=grid[0],
+                                 grid_w=grid[1], window_frames=1, capacity=K, query_tokens=1, kv_dtype=dtype)
+    wl = wl.with_(frames=2 + math.ceil(K / wl.tokens_per_frame) + 2)
+    h.log(f"case: EMA lists {dtype} T={wl.tokens_per_frame} K={K} C={C} streams={streams} frames={wl.frames}")
+    some = dict(sample=[0, 31], streams=streams, oracle_streams=[0, streams - 1]) if streams > 1 else {}
+    pair = h.Pair(wl, ema=True, alpha=0.05, beta=0.1, C=C, **some)
+    for f in range(wl.frames):
+        pair.step()
+    pair.check_bank(bitwise=True)
+
+
 @pytest.mark.parametrize("wl_name,theta,grid", [("7b", 1e4, 6), ("7b", 1e6, 6), ("7b", 1e4, 24), ("tiny", 1e4, 8)])
 def test_rope_readout(wl_name, theta, grid):
     """Rotary positions in the readout: near keys at their stream positions,
