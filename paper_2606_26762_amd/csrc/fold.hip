@@ -1797,16 +1797,21 @@ hipError_t launch_aggregate(const Dims& dm, const Workspace& ws, const FoldBatch
 //        form on MFMA (bound below) and list the pairs whose key and value
 //        partials may be below eps_k^2 and eps_v^2 (1e-4 relative slack for
 //        the float64 rounding of the exact sums, plus the Gram bound);
-//     b. groups of 16 lanes test the listed pairs exactly and mark those
-//        that merge in a bitmask [block rows][K];
+//     b. groups of 16 lanes test the listed pairs exactly, mark those that
+//        merge in a bitmask [block rows][K] and bring the rest of their rows
+//        into L2;
 //     c. wave 0 walks the marked rows: while i's centre has not moved, its
 //        partners are the marked j still holding mass (neither centre has
-//        changed since: a later slot only loses its mass to an earlier row);
-//        after i's first merge, and for rows whose pairs overflowed the
+//        changed since: a later slot only loses its mass to an earlier row),
+//        merged without another test; after i's first merge, and for rows whose pairs overflowed the
 //        list, it runs the filter as float32 sums of squares, 64 candidates
 //        at a time, and tests each candidate exactly (64 lanes, same tree).
 //     i absorbs j: sums, squared sums, histograms, n and n_res add, mu the
 //     mass-weighted mean; i's centre (registers and LDS) moves at once.
+//     The walk is a serial chain, so it is bound by latency: both rows are
+//     read whole in one round trip with i's row kept in registers, and the
+//     filter takes i's dims by lane reads (112 units, about 5 merges each:
+//     k_maintain 79 -> 47 us a fold; 15 without merges).
 //  3. Recycling (waves over a worklist): the empty slots, in ascending
 //     order, take the near window's tokens, newest frame first, raster order.
 //  4. The screening copies of aged and absorbing slots are rewritten
@@ -1866,6 +1871,11 @@ __device__ __forceinline__ void mt_dist16(const float2 (&ak)[4], const float2 (&
     dk = dk + __shfl_xor(dk, o, 64);
     dv = dv + __shfl_xor(dv, o, 64);
   }
+}
+
+// lane l's x in every lane (l uniform)
+__device__ __forceinline__ float lane_at(float x, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
 }
 
 template <int FP32, int FD>
@@ -2113,10 +2123,19 @@ __global__ __launch_bounds__(MT_THREADS) void k_maintain(Dims dm, Workspace ws, 
           }
           double dk, dv;
           mt_dist16(ak[h], av[h], bk[h], bv[h], dk, dv);
-          if (ok[h] && m == 0 && dk < ek2 && dv < ev2) {
+          if (ok[h] && dk < ek2 && dv < ev2) {  // (the same in the group's 16 lanes)
             const int li = pi[h] - r0;
-            atomicOr(&s_adj[li * W32 + (pj[h] >> 5)], 1u << (pj[h] & 31));
-            atomicOr(&s_rf[li >> 5], 1u << (li & 31));
+            if (m == 0) {
+              atomicOr(&s_adj[li * W32 + (pj[h] >> 5)], 1u << (pj[h] & 31));
+              atomicOr(&s_rf[li >> 5], 1u << (li & 31));
+            }
+            // the rest of both rows into L2 for the merge: lane m touches the
+            // m-th 128 bytes from the squared sums on (and the meta's)
+            const uint32_t* ti = reinterpret_cast<const uint32_t*>(rows + (size_t)pi[h] * ROW + ROW_SQK);
+            const uint32_t* tj = reinterpret_cast<const uint32_t*>(rows + (size_t)pj[h] * ROW + ROW_SQK);
+            const uint32_t x = ti[m * 32], y = tj[m * 32];
+            const uint32_t z = (m & 1 ? ti : tj)[(ROW_META - ROW_SQK) / 4];
+            asm volatile("" ::"v"(x), "v"(y), "v"(z));
           }
         }
       }
@@ -2136,8 +2155,13 @@ __global__ __launch_bounds__(MT_THREADS) void k_maintain(Dims dm, Workspace ws, 
           uint8_t* rowi = rows + (size_t)i * ROW;
           // scan: pick candidates with the filter (after a merge, or when the
           // row's pairs overflowed the list); else from the bitmask
-          bool scan = (ovw >> li) & 1u, have_ci = false;
-          float2 cik = make_float2(0.f, 0.f), civ = make_float2(0.f, 0.f);  // dims 2l, 2l+1 of c_i, p_i
+          bool scan = (ovw >> li) & 1u, have_i = false;
+          // row i, read with its first candidate's and then kept here: lane l
+          // holds dims 2l, 2l + 1 of the four sums and histogram words 4l ..
+          // 4l + 3 (H^K then H^V)
+          float2 xi[4], cik, civ;  // cik, civ: the same dims of c_i, p_i
+          uint4 hi;
+          RowMeta mi;
           int j0 = i + 1;
           while (j0 < A) {  // uniform
             int jj;
@@ -2158,12 +2182,14 @@ __global__ __launch_bounds__(MT_THREADS) void k_maintain(Dims dm, Workspace ws, 
             } else {
               const int j = j0 + lane;
               bool pass = false;
+              float ci = s_c16[(lane & (2 * FD - 1)) * dm.K + i];  // lane d: filter dim d of i
+              asm volatile("" : "+v"(ci));  // (read by every lane, not only those of the branch below)
               if (j < A && s_n[j] != 0) {
                 float pk = 0.f, pv = 0.f;
 #pragma unroll
                 for (int d = 0; d < FD; ++d) {
-                  const float dk = s_c16[d * dm.K + i] - s_c16[d * dm.K + j];
-                  const float dv = s_c16[(FD + d) * dm.K + i] - s_c16[(FD + d) * dm.K + j];
+                  const float dk = lane_at(ci, d) - s_c16[d * dm.K + j];
+                  const float dv = lane_at(ci, FD + d) - s_c16[(FD + d) * dm.K + j];
                   pk = pk + dk * dk;
                   pv = pv + dv * dv;
                 }
@@ -2176,66 +2202,62 @@ __global__ __launch_bounds__(MT_THREADS) void k_maintain(Dims dm, Workspace ws, 
               }
               jj = j0 + __ffsll((long long)bal) - 1;
             }
-            const uint8_t* rowj = rows + (size_t)jj * ROW;
-            if (!have_ci) {
-              const float ni = (float)s_n[i];
-              const float2 sk = reinterpret_cast<const float2*>(rowi + ROW_SUMK)[lane];
-              const float2 sv = reinterpret_cast<const float2*>(rowi + ROW_SUMV)[lane];
-              cik = make_float2(sk.x / ni, sk.y / ni);
-              civ = make_float2(sv.x / ni, sv.y / ni);
-              have_ci = true;
+            // the whole of both rows in one go: nearly every candidate merges
+            uint8_t* rowj = rows + (size_t)jj * ROW;
+            float2 xj[4];
+#pragma unroll
+            for (int a = 0; a < 4; ++a) xj[a] = reinterpret_cast<const float2*>(rowj + a * 512)[lane];
+            const uint4 hj = reinterpret_cast<const uint4*>(rowj + ROW_HK)[lane];
+            const RowMeta mj = *reinterpret_cast<const RowMeta*>(rowj + ROW_META);
+            if (!have_i) {
+#pragma unroll
+              for (int a = 0; a < 4; ++a) xi[a] = reinterpret_cast<const float2*>(rowi + a * 512)[lane];
+              hi = reinterpret_cast<const uint4*>(rowi + ROW_HK)[lane];
+              mi = *reinterpret_cast<const RowMeta*>(rowi + ROW_META);
+              const float ni = (float)mi.n;
+              cik = make_float2(xi[0].x / ni, xi[0].y / ni);
+              civ = make_float2(xi[1].x / ni, xi[1].y / ni);
+              have_i = true;
             }
-            const float nj = (float)s_n[jj];
-            const float2 tk = reinterpret_cast<const float2*>(rowj + ROW_SUMK)[lane];
-            const float2 tv = reinterpret_cast<const float2*>(rowj + ROW_SUMV)[lane];
-            const float2 cjk = make_float2(tk.x / nj, tk.y / nj), cjv = make_float2(tv.x / nj, tv.y / nj);
-            double dk, dv;
-            {
+            bool merge = true;  // a marked pair has passed the exact test, and neither centre has moved since
+            if (scan) {
+              const float nj = (float)mj.n;
+              const float2 cjk = make_float2(xj[0].x / nj, xj[0].y / nj), cjv = make_float2(xj[1].x / nj, xj[1].y / nj);
               const double ax = (double)cik.x - (double)cjk.x, ay = (double)cik.y - (double)cjk.y;
               const double bx = (double)civ.x - (double)cjv.x, by = (double)civ.y - (double)cjv.y;
-              dk = ax * ax + ay * ay;
-              dv = bx * bx + by * by;
+              double dk = ax * ax + ay * ay, dv = bx * bx + by * by;
 #pragma unroll
               for (int o = 32; o >= 1; o >>= 1) {
                 dk = dk + __shfl_xor(dk, o, 64);
                 dv = dv + __shfl_xor(dv, o, 64);
               }
+              merge = dk < ek2 && dv < ev2;
             }
-            if (dk < ek2 && dv < ev2) {  // uniform
-              // i absorbs jj: lane l adds dims 2l, 2l+1 of the four sums and
-              // histogram words 4l .. 4l+3 (H^K then H^V)
-              float2 x[4];
+            if (merge) {  // uniform
+              // i absorbs jj
 #pragma unroll
               for (int a = 0; a < 4; ++a) {
-                float2* pi = reinterpret_cast<float2*>(rowi + a * 512) + lane;
-                const float2 xi = *pi, xj = reinterpret_cast<const float2*>(rowj + a * 512)[lane];
-                x[a] = make_float2(xi.x + xj.x, xi.y + xj.y);
-                *pi = x[a];
+                xi[a] = make_float2(xi[a].x + xj[a].x, xi[a].y + xj[a].y);
+                reinterpret_cast<float2*>(rowi + a * 512)[lane] = xi[a];
               }
-              {
-                uint4* hi = reinterpret_cast<uint4*>(rowi + ROW_HK) + lane;
-                const uint4 h1 = *hi, h2 = reinterpret_cast<const uint4*>(rowj + ROW_HK)[lane];
-                *hi = make_uint4(h1.x + h2.x, h1.y + h2.y, h1.z + h2.z, h1.w + h2.w);
-              }
-              const RowMeta mi = *reinterpret_cast<const RowMeta*>(rowi + ROW_META);
-              const RowMeta mj = *reinterpret_cast<const RowMeta*>(rowj + ROW_META);
+              hi = make_uint4(hi.x + hj.x, hi.y + hj.y, hi.z + hj.z, hi.w + hj.w);
+              reinterpret_cast<uint4*>(rowi + ROW_HK)[lane] = hi;
               const float wi = (float)mi.n, wj = (float)mj.n, wsum = wi + wj;
-              RowMeta mn = mi;
-              mn.mu_x = ((wi * mi.mu_x) + (wj * mj.mu_x)) / wsum;
-              mn.mu_y = ((wi * mi.mu_y) + (wj * mj.mu_y)) / wsum;
-              mn.n = mi.n + mj.n;
-              mn.n_res = mi.n_res + mj.n_res;
+              mi.mu_x = ((wi * mi.mu_x) + (wj * mj.mu_x)) / wsum;
+              mi.mu_y = ((wi * mi.mu_y) + (wj * mj.mu_y)) / wsum;
+              mi.n += mj.n;
+              mi.n_res += mj.n_res;
               if (lane == 0) {
-                *reinterpret_cast<RowMeta*>(rowi + ROW_META) = mn;
-                *reinterpret_cast<uint32_t*>(const_cast<uint8_t*>(rowj) + ROW_META) = 0u;  // RowMeta::n
-                s_n[i] = mn.n;
+                *reinterpret_cast<RowMeta*>(rowi + ROW_META) = mi;
+                *reinterpret_cast<uint32_t*>(rowj + ROW_META) = 0u;  // RowMeta::n
+                s_n[i] = mi.n;
                 s_n[jj] = 0u;
                 s_dirty[i] = 1;
               }
               // i's centre moves
-              const float nn = (float)mn.n;
-              cik = make_float2(x[0].x / nn, x[0].y / nn);
-              civ = make_float2(x[1].x / nn, x[1].y / nn);
+              const float nn = (float)mi.n;
+              cik = make_float2(xi[0].x / nn, xi[0].y / nn);
+              civ = make_float2(xi[1].x / nn, xi[1].y / nn);
               if (lane < FD / 2) {
                 s_c16[(2 * lane) * dm.K + i] = cik.x;
                 s_c16[(2 * lane + 1) * dm.K + i] = cik.y;
