@@ -1856,7 +1856,7 @@ __global__ __launch_bounds__(NW * 64, 1) void k_attend_bf16(Dims dm, Workspace w
             }
           }
         }
-        if (kv == 1 && tail) {  // weight 0, but 0 x inf would not be 0
+        if (tail) {  // score -inf and weight 0, but unwritten centres or rotation tables may hold inf or NaN
 #pragma unroll
           for (int i = 0; i < 8; ++i) {
             xl[i] = ok ? xl[i] : 0.f;
