@@ -1513,7 +1513,7 @@ __global__ __launch_bounds__(256, EMA ? 2 : (NP > 2 ? 3 : 4)) void k_aggregate(D
 // With EMA centres the workgroup's 16 groups go on together: when a slot each
 // is absorbed and the tokens' residuals are in the workspace, the waves code
 // them as the screen does (pq_pair) and add the codes to the histograms by
-// integer atomics: 112 units x 196 tokens, K = 256, 50 -> 43 us against
+// integer atomics: 112 units x 196 tokens, K = 256, 49 -> 40 us against
 // workgroups over 32 fixed slots whose threads formed the sequential distances
 // themselves (running means 18, and the screen 12 less with EMA centres: the
 // codes' histogram lines are fetched here).  168 registers: the coding's
@@ -1811,7 +1811,8 @@ hipError_t launch_aggregate(const Dims& dm, const Workspace& ws, const FoldBatch
 //     The walk is a serial chain, so it is bound by latency: both rows are
 //     read whole in one round trip with i's row kept in registers, and the
 //     filter takes i's dims by lane reads (112 units, about 5 merges each:
-//     k_maintain 79 -> 47 us a fold; 15 without merges).
+//     47 us a fold, 15 without merges; four such frames folded one after the
+//     other and the bank read 690 -> 560 us).
 //  3. Recycling (waves over a worklist): the empty slots, in ascending
 //     order, take the near window's tokens, newest frame first, raster order.
 //  4. The screening copies of aged and absorbing slots are rewritten
