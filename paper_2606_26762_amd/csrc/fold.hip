@@ -1810,9 +1810,12 @@ hipError_t launch_aggregate(const Dims& dm, const Workspace& ws, const FoldBatch
 //     mass-weighted mean; i's centre (registers and LDS) moves at once.
 //     The walk is a serial chain, so it is bound by latency: both rows are
 //     read whole in one round trip with i's row kept in registers, and the
-//     filter takes i's dims by lane reads (112 units, about 5 merges each:
-//     47 us a fold, 15 without merges; four such frames folded one after the
-//     other and the bank read 690 -> 560 us).
+//     filter takes i's dims by lane reads.  Its control flow is scalar, so
+//     every lane is active at those reads (112 units, the same four frames
+//     over and over: 57 us a fold, 18 without merges; 68 with the reads under
+//     a divergent branch, where nothing kept a copy of the register whole, and
+//     more than that with all of them before the branch, in 32 scalar
+//     registers; 102 with both rows read again for every candidate).
 //  3. Recycling (waves over a worklist): the empty slots, in ascending
 //     order, take the near window's tokens, newest frame first, raster order.
 //  4. The screening copies of aged and absorbing slots are rewritten
@@ -1874,6 +1877,8 @@ __device__ __forceinline__ void mt_dist16(const float2 (&ak)[4], const float2 (&
   }
 }
 
+// x, the same in every lane, in a scalar register
+__device__ __forceinline__ uint32_t uniform(uint32_t x) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)x); }
 // lane l's x in every lane (l uniform)
 __device__ __forceinline__ float lane_at(float x, int l) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), l));
@@ -2146,13 +2151,13 @@ __global__ __launch_bounds__(MT_THREADS) void k_maintain(Dims dm, Workspace ws, 
     // 2c. merging (wave 0), marked rows ascending
     if (wave == 0) {
       for (int w = 0; w < (r1 - r0 + 31) / 32; ++w) {
-        const uint32_t ovw = s_ov[w];
-        uint32_t rword = s_rf[w] | ovw;
+        const uint32_t ovw = uniform(s_ov[w]);
+        uint32_t rword = uniform(s_rf[w]) | ovw;
         while (rword != 0u) {  // uniform
           const int li = w * 32 + __ffs(rword) - 1;
           rword &= rword - 1u;
           const int i = r0 + li;
-          if (s_n[i] == 0) continue;  // uniform
+          if (uniform(s_n[i]) == 0) continue;
           uint8_t* rowi = rows + (size_t)i * ROW;
           // scan: pick candidates with the filter (after a merge, or when the
           // row's pairs overflowed the list); else from the bitmask
@@ -2174,28 +2179,33 @@ __global__ __launch_bounds__(MT_THREADS) void k_maintain(Dims dm, Workspace ws, 
               const unsigned long long nz = __ballot(wv != 0u);
               if (nz == 0ull) break;
               const int wl = __ffsll((long long)nz) - 1;
-              const uint32_t wsel = __shfl(wv, wl, 64);
+              const uint32_t wsel = (uint32_t)__builtin_amdgcn_readlane((int)wv, wl);
               jj = wl * 32 + __ffs(wsel) - 1;
-              if (s_n[jj] == 0) {  // merged away meanwhile
+              if (uniform(s_n[jj]) == 0) {  // merged away meanwhile
                 j0 = jj + 1;
                 continue;
               }
             } else {
-              const int j = j0 + lane;
-              bool pass = false;
-              float ci = s_c16[(lane & (2 * FD - 1)) * dm.K + i];  // lane d: filter dim d of i
-              asm volatile("" : "+v"(ci));  // (read by every lane, not only those of the branch below)
-              if (j < A && s_n[j] != 0) {
-                float pk = 0.f, pv = 0.f;
+              // every lane scores a slot (past A the last one's), so that i's
+              // dims are read from lanes that take part
+              const int j = min(j0 + lane, A - 1);
+              const float ci = s_c16[(lane & (2 * FD - 1)) * dm.K + i];  // lane d: filter dim d of i
+              float ck[FD], cv[FD], pk = 0.f, pv = 0.f;
 #pragma unroll
-                for (int d = 0; d < FD; ++d) {
-                  const float dk = lane_at(ci, d) - s_c16[d * dm.K + j];
-                  const float dv = lane_at(ci, FD + d) - s_c16[(FD + d) * dm.K + j];
-                  pk = pk + dk * dk;
-                  pv = pv + dv * dv;
-                }
-                pass = !(pk > fk2) && !(pv > fv2);
+              for (int d = 0; d < FD; ++d) {
+                ck[d] = s_c16[d * dm.K + j];
+                cv[d] = s_c16[(FD + d) * dm.K + j];
               }
+              const uint32_t nj0 = s_n[j];
+              __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+              for (int d = 0; d < FD; ++d) {
+                const float dk = lane_at(ci, d) - ck[d], dv = lane_at(ci, FD + d) - cv[d];
+                pk = pk + dk * dk;
+                pv = pv + dv * dv;
+                if (d % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+              }
+              const bool pass = j0 + lane < A && nj0 != 0 && !(pk > fk2) && !(pv > fv2);
               const unsigned long long bal = __ballot(pass);
               if (bal == 0ull) {
                 j0 += 64;
@@ -2232,7 +2242,7 @@ __global__ __launch_bounds__(MT_THREADS) void k_maintain(Dims dm, Workspace ws, 
                 dk = dk + __shfl_xor(dk, o, 64);
                 dv = dv + __shfl_xor(dv, o, 64);
               }
-              merge = dk < ek2 && dv < ev2;
+              merge = __ballot(dk < ek2 && dv < ev2) != 0ull;  // (the same in every lane)
             }
             if (merge) {  // uniform
               // i absorbs jj

@@ -1,0 +1,50 @@
+"""CPU: the gfx950 code of the built library, disassembled."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+from paper_2606_26762_amd import protokv as pk
+
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """{mangled name: instructions} of every kernel."""
+    if not os.path.exists(OBJDUMP):
+        pytest.skip("no llvm-objdump")
+    d = tmp_path_factory.mktemp("code")
+    so = shutil.copy(pk.LIB_PATH, d / "lib.so")
+    subprocess.run([OBJDUMP, "--offloading", so], cwd=d, check=True, capture_output=True)
+    out = {}
+    for f in sorted(d.glob("*gfx950*")):
+        text = subprocess.run([OBJDUMP, "-d", f], check=True, capture_output=True, text=True).stdout
+        for name, body in re.findall(r"^[0-9a-f]+ <(\w+)>:\n((?:\t.*\n)+)", text, re.M):
+            out[name] = [l.split("//")[0].strip() for l in body.splitlines()]
+    assert out
+    return out
+
+
+def test_maintenance_reads_lanes_with_all_lanes_active(kernels):
+    """The merge scan reads a slot's filter dims from the lanes that hold them.
+    A register that a divergent branch copies or reloads is written in the
+    active lanes only, so those reads stand outside every such branch: the last
+    write of exec before them does not narrow it.  (Reads of the registers that
+    v_writelane fills are scalar spills and read no other lane's value.)"""
+    found = 0
+    for name, code in kernels.items():
+        if "k_maintain" not in name:
+            continue
+        spill = {m.group(1) for l in code if (m := re.match(r"v_writelane_b32 (v\d+),", l))}
+        last = ""
+        for l in code:
+            if re.match(r"s_\w+ exec,|s_\w*saveexec", l):
+                last = l
+            m = re.match(r"v_readlane_b32 s\d+, (v\d+), \d+", l)
+            if m and m.group(1) not in spill:
+                found += 1
+                assert "and_saveexec" not in last, f"{name}: {l} after {last}"
+    assert found >= 6 * 8   # six kernels, at least four dims of K and of V
