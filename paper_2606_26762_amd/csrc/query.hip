@@ -163,31 +163,6 @@ __device__ void decode_top_s(const uint32_t* hist /* [G][CMAX] */, int C, int S,
   for (int s = 0; s < S; ++s) out_codes[s] = s < nb ? bv.code[bv.at(cur, s, tl)] : 0u;
 }
 
-// Register-resident exact top-S for prototypes whose residual count is at
-// most 65534: every factor H+1 is below 2^16, so a product of 8 factors fits
-// in 128 bits.  Same beam (width S) and merge order as decode_top_s.
-struct U128 {
-  uint64_t lo, hi;
-};
-
-__device__ __forceinline__ U128 mul_u128_u32(const U128& a, uint32_t f) {
-  U128 r;
-  const unsigned __int128 t0 = (unsigned __int128)a.lo * f;
-  r.lo = (uint64_t)t0;
-  r.hi = a.hi * (uint64_t)f + (uint64_t)(t0 >> 64);
-  return r;
-}
-
-// Decoding with counts above 4094: two lanes per (slot, K/V) beam, 32 beams per
-// wave, for prototypes whose residual count is at most 65534 (every factor H+1
-// is below 2^16, so a product of the 8 factors fits in 128 bits) and S <= SM.
-// Lane q of a beam owns the prefixes e = q, q + 2, ...  For each subspace the
-// lanes sort the codewords (count desc, code asc), publish the top R = min(S, C)
-// in order through LDS, and merge: S pops of the best row head (product desc,
-// packed tuple asc), the best found in-lane and then with a DPP exchange with
-// the beam's other lane; only the winning row advances.  Same beam (width S) and
-// order as decode_top_s.
-
 // Exchanges within a quad of lanes (DPP quad_perm, no LDS round trip).
 template <int CTRL>
 __device__ __forceinline__ uint32_t qperm(uint32_t x) {
@@ -199,227 +174,9 @@ __device__ __forceinline__ uint64_t qperm64(uint64_t x) {
 }
 constexpr int QP_XOR1 = 0xB1;  // lanes (1, 0, 3, 2)
 
-// (pa, ca) ranks before (pb, cb), without branches
-__device__ __forceinline__ bool before128b(const U128& pa, uint32_t ca, const U128& pb, uint32_t cb) {
-  const bool gh = pa.hi > pb.hi, eh = pa.hi == pb.hi, gl = pa.lo > pb.lo, el = pa.lo == pb.lo;
-  return gh | (eh & (gl | (el & (ca < cb))));
-}
 __device__ __forceinline__ uint64_t sel64(bool t, uint64_t a, uint64_t b) {
   const uint64_t m = 0ull - (uint64_t)t;
   return (a & m) | (b & ~m);
-}
-__device__ __forceinline__ uint32_t sel32(bool t, uint32_t a, uint32_t b) {
-  const uint32_t m = 0u - (uint32_t)t;
-  return (a & m) | (b & ~m);
-}
-
-// Product helpers of the decode merge: 64-bit or 128-bit unsigned products.
-template <typename P> __device__ __forceinline__ P pt_from(uint32_t x);
-template <> __device__ __forceinline__ uint64_t pt_from<uint64_t>(uint32_t x) { return x; }
-template <> __device__ __forceinline__ U128 pt_from<U128>(uint32_t x) { return U128{x, 0ull}; }
-__device__ __forceinline__ uint64_t pt_mul(uint64_t a, uint32_t f) { return a * f; }
-__device__ __forceinline__ U128 pt_mul(const U128& a, uint32_t f) { return mul_u128_u32(a, f); }
-__device__ __forceinline__ bool pt_before(uint64_t pa, uint32_t ca, uint64_t pb, uint32_t cb) {
-  return (pa > pb) | ((pa == pb) & (ca < cb));
-}
-__device__ __forceinline__ bool pt_before(const U128& pa, uint32_t ca, const U128& pb, uint32_t cb) {
-  return before128b(pa, ca, pb, cb);
-}
-__device__ __forceinline__ uint64_t pt_sel(bool t, uint64_t a, uint64_t b) { return sel64(t, a, b); }
-__device__ __forceinline__ U128 pt_sel(bool t, const U128& a, const U128& b) {
-  return U128{sel64(t, a.lo, b.lo), sel64(t, a.hi, b.hi)};
-}
-template <int CTRL> __device__ __forceinline__ uint64_t pt_perm(uint64_t x) { return qperm64<CTRL>(x); }
-template <int CTRL> __device__ __forceinline__ U128 pt_perm(const U128& x) {
-  return U128{qperm64<CTRL>(x.lo), qperm64<CTRL>(x.hi)};
-}
-
-// The beam merge (S <= 16, large counts) for one product type P (uint64_t when every
-// product of the wave's beams fits in 64 bits, else U128): products of the
-// factors H+1 compare exactly either way.
-template <int SM, typename P>
-__device__ __forceinline__ void decode_beam(uint32_t (*s_rank)[CMAX], const uint32_t* hist, bool mine, int S,
-                                            int C, int q, int bq, uint32_t* out) {
-  constexpr int LPB = 2;             // lanes per beam
-  constexpr int E = SM / LPB;        // prefixes per lane
-  constexpr int KPL = CMAX / LPB;    // codewords per lane
-  const int R = S < C ? S : C;
-  P pp[E];
-  uint32_t pc[E];
-#pragma unroll
-  for (int j = 0; j < E; ++j) {
-    pp[j] = pt_from<P>((q == 0 && j == 0) ? 1u : 0u);
-    pc[j] = 0;
-  }
-  int nb = 1;
-  // this lane's counts of subspace g, loaded one subspace ahead
-  uint4 hnext[KPL / 4];
-#pragma unroll
-  for (int v4 = 0; v4 < KPL / 4; ++v4)
-    hnext[v4] = mine ? reinterpret_cast<const uint4*>(hist)[q * (KPL / 4) + v4] : make_uint4(0, 0, 0, 0);
-  for (int g = 0; g < G; ++g) {
-    uint4 hcur[KPL / 4];
-#pragma unroll
-    for (int v4 = 0; v4 < KPL / 4; ++v4) {
-      hcur[v4] = hnext[v4];
-      hnext[v4] = mine && g + 1 < G ? reinterpret_cast<const uint4*>(hist + (g + 1) * CMAX)[q * (KPL / 4) + v4]
-                                    : make_uint4(0, 0, 0, 0);
-    }
-    // keys of codewords KPL q .. KPL q + KPL - 1: (count << 4 | (15 - c)) + 1,
-    // larger = better, 0 = absent
-    uint32_t key[KPL];
-#pragma unroll
-    for (int v4 = 0; v4 < KPL / 4; ++v4) {
-      const uint4 h4 = hcur[v4];
-      const uint32_t hv[4] = {h4.x, h4.y, h4.z, h4.w};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int c = KPL * q + 4 * v4 + i;
-        key[4 * v4 + i] = c < C ? ((hv[i] << 4) | (uint32_t)(15 - c)) + 1u : 0u;
-      }
-    }
-    // ranks of the 16 keys (unique: the code is in the low bits)
-    // each lane sorts its 8 keys descending (bitonic network), then one
-    // bitonic half-cleaner across the pair (lane 0 keeps the larger of
-    // key[k] and the partner's key[7 - k], lane 1 the smaller) and a
-    // bitonic merge of 8 leave lane 0 with ranks 0..7 and lane 1 with
-    // ranks 8..15, both in order
-    auto cx = [&](int a, int b, bool desc) {
-      const uint32_t x = key[a], y = key[b];
-      const uint32_t hi = x > y ? x : y, lo = x > y ? y : x;
-      key[a] = desc ? hi : lo;
-      key[b] = desc ? lo : hi;
-    };
-#pragma unroll
-    for (int k = 2; k <= KPL; k <<= 1)
-#pragma unroll
-      for (int j = k >> 1; j > 0; j >>= 1)
-#pragma unroll
-        for (int i = 0; i < KPL; ++i)
-          if ((i ^ j) > i) cx(i, i ^ j, (i & k) == 0);
-    uint32_t t[KPL];
-#pragma unroll
-    for (int k = 0; k < KPL; ++k) t[k] = qperm<QP_XOR1>(key[KPL - 1 - k]);
-#pragma unroll
-    for (int k = 0; k < KPL; ++k) {
-      const uint32_t hi = key[k] > t[k] ? key[k] : t[k], lo = key[k] > t[k] ? t[k] : key[k];
-      key[k] = q == 0 ? hi : lo;
-    }
-#pragma unroll
-    for (int j = KPL >> 1; j > 0; j >>= 1)
-#pragma unroll
-      for (int i = 0; i < KPL; ++i)
-        if ((i ^ j) > i) cx(i, i ^ j, true);
-#pragma unroll
-    for (int i = 0; i < KPL; ++i)
-      if (key[i] != 0u && q * KPL + i < R) s_rank[bq][q * KPL + i] = key[i];
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const int shift = 4 * (G - 1 - g);
-    if (g == 0) {
-      // one prefix (the empty tuple): the beam is the ranks themselves
-#pragma unroll
-      for (int j = 0; j < E; ++j) {
-        const int e = q + LPB * j;
-        const uint32_t ke = s_rank[bq][e < R ? e : 0];
-        pp[j] = pt_from<P>(e < R ? ((ke - 1u) >> 4) + 1u : 0u);
-        pc[j] = e < R ? (15u - ((ke - 1u) & 15u)) << shift : 0u;
-      }
-      nb = S < R ? S : R;
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      continue;
-    }
-    const uint32_t k0 = s_rank[bq][0];
-    // row heads: prefix e = q + LPB j times rank ptr[j]
-    int ptr[E];
-    P hp[E];
-    uint32_t hc[E];
-#pragma unroll
-    for (int j = 0; j < E; ++j) {
-      ptr[j] = 0;
-      const bool ok = q + LPB * j < nb;
-      hp[j] = ok ? pt_mul(pp[j], ((k0 - 1u) >> 4) + 1u) : pt_from<P>(0u);
-      hc[j] = ok ? (pc[j] | ((15u - ((k0 - 1u) & 15u)) << shift)) : 0xFFFFFFFFu;
-    }
-    const int nout = S < nb * R ? S : nb * R;
-    P np[E];
-    uint32_t nc[E];
-#pragma unroll
-    for (int j = 0; j < E; ++j) { np[j] = pt_from<P>(0u); nc[j] = 0; }
-#pragma unroll
-    for (int o = 0; o < SM; ++o) {
-      if (o < nout) {
-        // best head of this lane (product 0 = exhausted row)
-        P bv = hp[0];
-        uint32_t bc = hc[0];
-        int bj = 0;
-#pragma unroll
-        for (int j = 1; j < E; ++j) {
-          const bool t = pt_before(hp[j], hc[j], bv, bc);
-          bv = pt_sel(t, hp[j], bv);
-          bc = sel32(t, hc[j], bc);
-          bj = t ? j : bj;
-        }
-        uint32_t who = (uint32_t)(q * E + bj);
-        // best of the beam's lanes
-        {
-          const P ov = pt_perm<QP_XOR1>(bv);
-          const uint32_t oc = qperm<QP_XOR1>(bc), ow = qperm<QP_XOR1>(who);
-          const bool t = pt_before(ov, oc, bv, bc);
-          bv = pt_sel(t, ov, bv);
-          bc = sel32(t, oc, bc);
-          who = sel32(t, ow, who);
-        }
-        {
-          const bool rec = (o % LPB) == q;
-          np[o / LPB] = pt_sel(rec, bv, np[o / LPB]);
-          nc[o / LPB] = sel32(rec, bc, nc[o / LPB]);
-        }
-        // the winning row moves to its next rank: one product, then selects
-        const bool iwin = (int)(who / E) == q;
-        const int j = (int)(who % E);
-        int pj = ptr[0];
-        P base = pp[0];
-        uint32_t bcode = pc[0];
-#pragma unroll
-        for (int jj = 1; jj < E; ++jj) {
-          const bool t = jj == j;
-          pj = t ? ptr[jj] : pj;
-          base = pt_sel(t, pp[jj], base);
-          bcode = sel32(t, pc[jj], bcode);
-        }
-        pj += 1;
-        const bool more = pj < R;
-        const uint32_t kk = s_rank[bq][more ? pj : 0];
-        const P nh = pt_sel(more, pt_mul(base, ((kk - 1u) >> 4) + 1u), pt_from<P>(0u));
-        const uint32_t ncode = more ? (bcode | ((15u - ((kk - 1u) & 15u)) << shift)) : 0xFFFFFFFFu;
-#pragma unroll
-        for (int jj = 0; jj < E; ++jj) {
-          const bool t = iwin && jj == j;
-          ptr[jj] = t ? pj : ptr[jj];
-          hp[jj] = pt_sel(t, nh, hp[jj]);
-          hc[jj] = sel32(t, ncode, hc[jj]);
-        }
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < E; ++j) { pp[j] = np[j]; pc[j] = nc[j]; }
-    nb = nout;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  }
-  if (mine) {
-#pragma unroll
-    for (int j = 0; j < E; ++j) {
-      const int o = q + LPB * j;
-      if (o < S) out[o] = o < nb ? pc[j] : 0u;
-    }
-    if (q == 0) out[SMAX] = 0u;
-  }
 }
 
 // Decoding by halves: the top SM tuples of subspaces 0..3 and of subspaces
@@ -431,14 +188,19 @@ __device__ __forceinline__ void decode_beam(uint32_t (*s_rank)[CMAX], const uint
 // codeword ranks come from 16-bit keys (H + 1) << 4 | (15 - c), two subspaces
 // in the halves of one register.  Half products from 2^37 (the four largest
 // counts of a half 600 in the geometric mean) are 64-bit integers above the
-// tuple instead, ordered by compares and selects; counts above 4094 are left to
-// decode_beam.
+// tuple instead, ordered by compares and selects; with counts above 4094 the
+// keys are whole registers and the tuple lies beside the 64-bit product, ordered
+// by both (slots of 60 000 residuals: 112 units x 256, S = 8, 28 us; 256 x 2 048,
+// S = 8, 320, and S = 12, 1 008; a beam search on two lanes in this kernel, which
+// took counts above 4094 before, 43, 578 and 2 940, and the kernels before the
+// decode by halves 53, 379 and 1 430).
 //
 // The joined product's ties are broken by the first half's tuple, then the
 // second's, whose order within one first half is its rank j: a tag of 2
 // log2(SM) bits (the tuple's rank among the SM first halves, SM - 1 - j).
 // Products below 2^53 / 2^tag carry it in the mantissa like the others; larger
-// ones (below 2^96) are compared as 54 + 42 bits with the tag below.
+// ones are compared as 54 + 42 bits (below 2^96) or 128 bits (large counts) with
+// the tag below.
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 // a <- the first in rank order of a and b, b <- the other
@@ -488,6 +250,45 @@ __device__ __forceinline__ void first2(Wide& a, const Wide& b) {
   a.hi = sel64(sw, b.hi, a.hi);
   a.lo = sel64(sw, b.lo, a.lo);
 }
+// Half products of large counts beside their inverted tuple, and products of two
+// of them beside their tag.
+struct Tagged64 {
+  uint64_t p;
+  uint32_t tag;
+};
+struct Tagged128 {
+  uint64_t hi, lo;
+  uint32_t tag;
+};
+// b comes before a in rank order
+__device__ __forceinline__ bool swapped(const Tagged64& a, const Tagged64& b) {
+  return (b.p > a.p) | ((b.p == a.p) & (b.tag > a.tag));
+}
+__device__ __forceinline__ bool swapped(const Tagged128& a, const Tagged128& b) {
+  return (b.hi > a.hi) | ((b.hi == a.hi) & ((b.lo > a.lo) | ((b.lo == a.lo) & (b.tag > a.tag))));
+}
+__device__ __forceinline__ Tagged64 pick(bool t, const Tagged64& a, const Tagged64& b) {
+  return Tagged64{t ? a.p : b.p, t ? a.tag : b.tag};
+}
+__device__ __forceinline__ Tagged128 pick(bool t, const Tagged128& a, const Tagged128& b) {
+  return Tagged128{t ? a.hi : b.hi, t ? a.lo : b.lo, t ? a.tag : b.tag};
+}
+template <typename E>
+__device__ __forceinline__ auto order2(E& a, E& b) -> decltype(pick(true, a, b), void()) {
+  const bool sw = swapped(a, b);
+  const E t = a;
+  a = pick(sw, b, a);
+  b = pick(sw, t, b);
+}
+template <typename E>
+__device__ __forceinline__ auto first2(E& a, const E& b) -> decltype(pick(true, a, b), void()) {
+  a = pick(swapped(a, b), b, a);
+}
+__device__ __forceinline__ void order2(uint32_t& a, uint32_t& b) {
+  const uint32_t hi = max(a, b), lo = min(a, b);
+  a = hi;
+  b = lo;
+}
 // bitonic sequence a[0..N-1] -> rank order
 template <int N, typename E>
 __device__ __forceinline__ void bitonic(E* a) {
@@ -505,7 +306,8 @@ __device__ __forceinline__ void keep_top(E (&a)[N], const E (&b)[M]) {
   bitonic<N>(a);
 }
 // Eight keys into rank order (Batcher's odd-even merge sort, 19 exchanges).
-__device__ __forceinline__ void sort8(u16x2* a) {
+template <typename E>
+__device__ __forceinline__ void sort8(E* a) {
   constexpr int X[19][2] = {{0, 1}, {2, 3}, {4, 5}, {6, 7}, {0, 2}, {1, 3}, {4, 6}, {5, 7}, {1, 2}, {5, 6},
                             {0, 4}, {1, 5}, {2, 6}, {3, 7}, {2, 4}, {3, 5}, {1, 2}, {3, 4}, {5, 6}};
 #pragma unroll
@@ -566,13 +368,16 @@ constexpr uint32_t HALF_TAG = 0xFFFFu;     // the inverted tuple in a half produ
 
 __device__ __forceinline__ uint32_t lo32(double x) { return (uint32_t)__double_as_longlong(x); }
 __device__ __forceinline__ uint32_t lo32(uint64_t x) { return (uint32_t)x; }
+__device__ __forceinline__ uint32_t lo32(const Tagged64& x) { return x.tag; }
 __device__ __forceinline__ double with_lo32(double x, uint32_t lo) {
   return __longlong_as_double((__double_as_longlong(x) & ~0xFFFFFFFFll) | lo);
 }
 __device__ __forceinline__ uint64_t with_lo32(uint64_t x, uint32_t lo) { return (x & ~0xFFFFFFFFull) | lo; }
+__device__ __forceinline__ Tagged64 with_lo32(const Tagged64& x, uint32_t lo) { return Tagged64{x.p, lo}; }
 // a half product x (tag clear) as an integer
 __device__ __forceinline__ uint64_t half_int(double x) { return (uint64_t)x; }
 __device__ __forceinline__ uint64_t half_int(uint64_t x) { return x >> 16; }
+__device__ __forceinline__ uint64_t half_int(const Tagged64& x) { return x.p; }
 // the value of lane CTRL's pattern in the quad
 template <int CTRL>
 __device__ __forceinline__ double half_perm(double x) {
@@ -580,6 +385,10 @@ __device__ __forceinline__ double half_perm(double x) {
 }
 template <int CTRL>
 __device__ __forceinline__ uint64_t half_perm(uint64_t x) { return qperm64<CTRL>(x); }
+template <int CTRL>
+__device__ __forceinline__ Tagged64 half_perm(const Tagged64& x) {
+  return Tagged64{qperm64<CTRL>(x.p), qperm<CTRL>(x.tag)};
+}
 
 // The counts of four subspaces, and the largest half product and count they
 // can give.
@@ -653,9 +462,47 @@ __device__ __forceinline__ void decode_half(const HalfCounts& hc, int C, E (&p)[
   }
 }
 
+// The same for counts up to 65534, read again from LDS: unit 4 g + v of the
+// half at `unit`.  One rolled loop over the subspaces, from the empty tuple.
+template <int SM, typename F>
+__device__ __forceinline__ void decode_half_large(F unit, int C, Tagged64 (&p)[SM]) {
+#pragma unroll
+  for (int i = 0; i < SM; ++i) p[i] = Tagged64{i == 0 ? 1ull : 0ull, 0u};
+#pragma nounroll
+  for (int g = 0; g < 4; ++g) {
+    uint32_t key[16];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const uint4 h = unit(4 * g + v);
+      const uint32_t x[4] = {h.x, h.y, h.z, h.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int c = 4 * v + e;
+        key[c] = c < C ? (x[e] << 4) + (uint32_t)(16 + 15 - c) : 0u;
+      }
+    }
+    sort8(key);
+    sort8(key + 8);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      if (SM == 16) order2(key[i], key[15 - i]);
+      else key[i] = max(key[i], key[15 - i]);
+    }
+    bitonic<8>(key);
+    if (SM == 16) bitonic<8>(key + 8);  // (in reversed places: still a bitonic sequence)
+    const int sh = 12 - 4 * g;
+    Tagged64 b[SM];
+#pragma unroll
+    for (int i = 0; i < SM; ++i) b[i] = p[i];
+    top_products(p, [&](int i, int j) {
+      return Tagged64{b[i].p * (key[j] >> 4), b[i].tag | (key[j] & 15u) << sh};
+    });
+  }
+}
+
 // The top S tuples from the halves' top SM (pa: subspaces 0..3, pb: 4..7), lane
 // q of the pair writing those of its parity.  `wide`: uniform, some lane's
-// product may not fit the mantissa beside its tag.  codes: 2 SM words of LDS per
+// product may not fit the mantissa beside its tag.  codes: 4 SM words of LDS per
 // lane at a stride of 64 words.
 template <int SM, typename E>
 __device__ __forceinline__ void decode_join(const E (&pa)[SM], const E (&pb)[SM], bool wide, bool mine, int S, int q,
@@ -702,13 +549,36 @@ __device__ __forceinline__ void decode_join(const E (&pa)[SM], const E (&pb)[SM]
       ia[i] = half_int(a[i]);
       ib[i] = half_int(b[i]);
     }
-    Wide r[SM];
-    top_products(r, [&](int i, int j) {
-      const unsigned __int128 x = (unsigned __int128)ia[i] * ib[j];
-      return Wide{(uint64_t)(x >> 42), ((uint64_t)x & ((1ull << 42) - 1)) << 8 | ra[i] | (uint32_t)(SM - 1 - j)};
-    });
+    if constexpr (std::is_same_v<E, Tagged64>) {
+      // (the second halves in LDS: SM = 16 then fits 256 registers, two waves
+      // a SIMD)
+      uint32_t* second_half = codes + 2 * SM * 64;
 #pragma unroll
-    for (int o = 0; o < SM; ++o) tag[o] = (uint32_t)r[o].lo & (SM * SM - 1);
+      for (int j = 0; j < SM; ++j) {
+        second_half[2 * j * 64] = (uint32_t)ib[j];
+        second_half[(2 * j + 1) * 64] = (uint32_t)(ib[j] >> 32);
+      }
+      asm volatile("" ::: "memory");
+      Tagged128 r[SM];
+      top_products(r, [&](int i, int j) {
+        const uint64_t b = (uint64_t)second_half[(2 * j + 1) * 64] << 32 | second_half[2 * j * 64];
+        const unsigned __int128 x = (unsigned __int128)ia[i] * b;
+        return Tagged128{(uint64_t)(x >> 64), (uint64_t)x, ra[i] | (uint32_t)(SM - 1 - j)};
+      });
+#pragma unroll
+      for (int o = 0; o < SM; ++o) {
+        tag[o] = r[o].tag;
+        asm("" : "+v"(tag[o]));
+      }
+    } else {
+      Wide r[SM];
+      top_products(r, [&](int i, int j) {
+        const unsigned __int128 x = (unsigned __int128)ia[i] * ib[j];
+        return Wide{(uint64_t)(x >> 42), ((uint64_t)x & ((1ull << 42) - 1)) << 8 | ra[i] | (uint32_t)(SM - 1 - j)};
+      });
+#pragma unroll
+      for (int o = 0; o < SM; ++o) tag[o] = (uint32_t)r[o].lo & (SM * SM - 1);
+    }
   }
   if (mine) {
 #pragma unroll
@@ -731,12 +601,13 @@ __device__ __forceinline__ void decode_join(const E (&pa)[SM], const E (&pb)[SM]
 // loads into registers 195, 197 with one lane per beam and sorting networks on
 // 64-bit products) or, on few slots, by one wave's 1 530 VALU instructions
 // (112 units x 256 slots: 32 -> 17 us; 64 slots 25 -> 7 us; S = 16 on 2 000
-// slots, two lanes and merge pops before, 63 -> 13.5 us).
+// slots, two lanes and merge pops before, 63 -> 13.5 us).  Two waves a SIMD, as the
+// LDS allows: with 262 registers S > 8 had one (112 x 256, S = 16, 49 -> 38 us).
 template <int SM>
-__global__ __launch_bounds__(256) void k_decode(Dims dm, Workspace ws, int sid, int n_active, int centres) {
+__global__ __launch_bounds__(256, 2) void k_decode(Dims dm, Workspace ws, int sid, int n_active, int centres) {
   constexpr int SPW = 16;  // slots per wave
   __shared__ __attribute__((aligned(16))) uint8_t s_mem[4][SPW * 1024];
-  static_assert(2 * SM * 64 * 4 <= SPW * 1024 && 32 * CMAX * 4 <= SPW * 1024, "tuples and ranks reuse the histograms' LDS");
+  static_assert(4 * SM * 64 * 4 <= SPW * 1024, "tuples and halves reuse the histograms' LDS");
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int nslots = dm.units * n_active;
@@ -762,7 +633,6 @@ __global__ __launch_bounds__(256) void k_decode(Dims dm, Workspace ws, int sid, 
   const int sl = min(slot0 + (lane >> 2), nslots - 1);
   const int u = sl / n_active, p = sl % n_active;
   const uint8_t* row = bank + ((size_t)u * dm.K + p) * ROW;
-  const uint32_t* hist = reinterpret_cast<const uint32_t*>(row + (kv ? ROW_HV : ROW_HK));
   const RowMeta m = *reinterpret_cast<const RowMeta*>(row + ROW_META);
   uint32_t* out = ws.pcodes + (((size_t)u * dm.K + p) * 2 + kv) * PCW;
   const bool pq = (dm.flags & PROTOKV_FLAG_PQ) != 0;
@@ -786,6 +656,9 @@ __global__ __launch_bounds__(256) void k_decode(Dims dm, Workspace ws, int sid, 
   const bool mine = bvalid && !nores && m.n_res <= 65534u && S <= SM;
   wait_vm<0>();  // the histograms have landed
   asm volatile("" ::: "memory");
+  auto unit = [&](int i) {  // 16 bytes of this lane's half
+    return *reinterpret_cast<const uint4*>(mem + (lane >> 2) * 1024 + (lane & 3) * 256 + ((i + lane) & 15) * 16);
+  };
   HalfCounts hc;
   hc.bound = 1.0;
   hc.most = 0;
@@ -794,8 +667,7 @@ __global__ __launch_bounds__(256) void k_decode(Dims dm, Workspace ws, int sid, 
     uint32_t mx = 0;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const uint4 x = *reinterpret_cast<const uint4*>(mem + (lane >> 2) * 1024 + (lane & 3) * 256 +
-                                                      ((4 * g + v + lane) & 15) * 16);
+      const uint4 x = unit(4 * g + v);
       hc.h[g][v] = x;
       mx = max(max(mx, max(x.x, x.y)), max(x.z, x.w));
     }
@@ -803,33 +675,25 @@ __global__ __launch_bounds__(256) void k_decode(Dims dm, Workspace ws, int sid, 
     hc.bound *= (double)mx + 1.0;
   }
   const double bound = hc.bound * __longlong_as_double((long long)qperm64<QP_XOR1>((uint64_t)__double_as_longlong(hc.bound)));
-  if (__all(!mine || hc.most <= HALF_COUNT)) {
-    const bool wide = !__all(!mine || bound < 0x1p53 / (SM * SM));
-    auto halves = [&](auto e) {
-      using E = decltype(e);
-      E pa[SM], pb[SM];
-      decode_half<SM, E>(hc, C, pa);
+  const bool wide = !__all(!mine || bound < 0x1p53 / (SM * SM));
+  auto halves = [&](auto e) {
+    using E = decltype(e);
+    E pa[SM], pb[SM];
+    if constexpr (std::is_same_v<E, Tagged64>) decode_half_large<SM>(unit, C, pa);
+    else decode_half<SM, E>(hc, C, pa);
 #pragma unroll
-      for (int i = 0; i < SM; ++i) {  // lanes (1, 1, 3, 3) and (0, 0, 2, 2) of each quad
-        pb[i] = half_perm<0xF5>(pa[i]);
-        pa[i] = half_perm<0xA0>(pa[i]);
-      }
-      decode_join<SM, E>(pa, pb, wide, mine, S, q, reinterpret_cast<uint32_t*>(mem) + lane, out);
-    };
-    if (__all(!mine || hc.bound < HALF_MAX))
-      halves(0.0);
-    else
-      halves((uint64_t)0);
-    return;
-  }
-  // every product the merge forms is at most prod_g max_c (H[g][c] + 1);
-  // when that fits in 64 bits for all of the wave's beams the merge runs on
-  // 64-bit products
-  uint32_t(*rank)[CMAX] = reinterpret_cast<uint32_t(*)[CMAX]>(mem);
-  if (__all(!mine || bound < 0x1p63))
-    decode_beam<SM, uint64_t>(rank, hist, mine, S, C, q, lane >> 1, out);
+    for (int i = 0; i < SM; ++i) {  // lanes (1, 1, 3, 3) and (0, 0, 2, 2) of each quad
+      pb[i] = half_perm<0xF5>(pa[i]);
+      pa[i] = half_perm<0xA0>(pa[i]);
+    }
+    decode_join<SM, E>(pa, pb, wide, mine, S, q, reinterpret_cast<uint32_t*>(mem) + lane, out);
+  };
+  if (__all(!mine || hc.bound < HALF_MAX) && __all(!mine || hc.most <= HALF_COUNT))
+    halves(0.0);
+  else if (__all(!mine || hc.most <= HALF_COUNT))
+    halves((uint64_t)0);
   else
-    decode_beam<SM, U128>(rank, hist, mine, S, C, q, lane >> 1, out);
+    halves(Tagged64{});
 }
 
 // Decoding, wide path (prototypes with more than 65534 residuals, whose

@@ -85,7 +85,7 @@ def _histograms(kind, C, rng):
 
 
 # S = 8 and 16 are the lists' own lengths; C = 2 has fewer codewords than
-# ranks; 256 units x 260 slots are more beams than two lanes each are used for
+# ranks; of 256 units x 260 slots, 16 to a wave, waves straddle units
 @pytest.mark.parametrize("S,C,units,cap", [(8, 16, 2, 40), (5, 12, 2, 40), (1, 2, 2, 40), (16, 16, 2, 40),
                                            (9, 2, 2, 40), (8, 16, 256, 260)])
 def test_decode_at_the_edges_of_its_products(S, C, units, cap):
@@ -126,6 +126,74 @@ def test_decode_at_the_edges_of_its_products(S, C, units, cap):
         gpu.synthesize(0)
         gk, gv, _ = gpu.read_pseudo()
         for u in sample:
+            ps = O.synthesize(h.bank_from_rows(bank, u, p), cb[u], p)
+            n = len(ps.keys)
+            assert np.array_equal(gk[u][:n], ps.keys) and np.array_equal(gv[u][:n], ps.values), f"{kind} unit {u}"
+
+
+def _large_histograms(kind, C, slot, rng):
+    """[8][C] counts of one slot, every subspace with the same total <= 65534."""
+    if kind == "mixed":   # one slot of a wave's 16 beyond 4094
+        kind = "descending to 7000" if slot % 16 == 5 else "descending to 40"
+    if kind.startswith("flat"):   # "flat n": products equal; "flat n -": nearly, and colliding
+        top = int(kind.split()[1])
+        base = np.full(C, top, dtype=np.int64)
+        if kind.endswith("-"):
+            base[rng.permutation(C)[:C // 2]] -= 1
+    elif kind.startswith("descending"):
+        top = int(kind.split()[-1])
+        base = np.array([top * (C - i) // C for i in range(C)], dtype=np.int64)
+    else:   # "peaks n": n codewords share 65534
+        n = int(kind.split()[1])
+        base = np.zeros(C, dtype=np.int64)
+        base[:n] = 65534 // n
+    return np.stack([base[rng.permutation(C)] for _ in range(8)])
+
+
+@pytest.mark.parametrize("S,C", [(8, 16), (16, 16), (3, 12), (9, 2), (16, 11)])
+def test_decode_of_large_counts(S, C):
+    """Exact top-S tuples of slots with thousands of residuals a codeword: half
+    products up to 4095^4 and joined ones up to 4095^8, 40 bits below and just
+    below what their formats hold, and beyond 4094 up to 65534 residuals in one
+    codeword, alone in a wave or throughout.  Rows bitwise against the oracle's."""
+    import ctypes
+    from oracle import protokv_oracle as O
+    h = H()
+    cap = 37
+    wl = W.WORKLOADS["7b"].with_(num_layers=2, num_kv_heads=1, num_q_heads=1, grid_h=7, grid_w=7, frames=0,
+                                 window_frames=2, capacity=cap, query_tokens=1)
+    p = h.oracle_params(wl, S=S, C=C, B=max(32, S))
+    cb = W.make_codebooks_device(wl, samples=256, iters=3, C=C)[0]
+    gpu = h.pk.ProtoKV(h.gpu_config(wl, p), cb)
+    gen = W.DeviceStream(wl)
+    for _ in range(4):
+        gpu.append_frame([0], *gen.next_frame())
+        gpu.fold()
+    state = gpu.get_state(0)
+    # a stream position that allows 65534 residuals a slot
+    hd, T = state.header, wl.tokens_per_frame
+    hd.folds = -(-65534 // T)
+    hd.frames, hd.evicted_tokens = hd.folds + wl.window_frames, hd.folds * T
+    state.blob[:ctypes.sizeof(hd)] = np.frombuffer(bytes(hd), dtype=np.uint8)
+    rng = np.random.default_rng(S * 100 + C)
+    for kind in ("flat 4094", "flat 4094 -", "descending to 4094", "flat 4095", "flat 4095 -", "descending to 7000",
+                 "mixed", "peaks 2", "peaks 1"):
+        h.log(f"case: decode of large counts {kind} S={S} C={C}")
+        bank = state.bank()
+        for u in range(wl.units):
+            for k in range(cap):
+                hist = [_large_histograms(kind, C, k, rng) for _ in range(2)]
+                bank["hist_k"][u, k, :, :C], bank["hist_v"][u, k, :, :C] = hist
+                n = int(hist[0][0].sum())
+                assert n <= 65534 and all(int(x.sum(axis=1).max()) == int(x.sum(axis=1).min()) == n for x in hist)
+                bank["n_res"][u, k], bank["n"][u, k] = n, n + 1
+        rows = h.pk.encode_bank(bank, wl.units, cap).reshape(wl.units, -1)
+        for u in range(wl.units):
+            state.set_bank_rows(u, rows[u])
+        gpu.set_state(0, state)
+        gpu.synthesize(0)
+        gk, gv, _ = gpu.read_pseudo()
+        for u in range(wl.units):
             ps = O.synthesize(h.bank_from_rows(bank, u, p), cb[u], p)
             n = len(ps.keys)
             assert np.array_equal(gk[u][:n], ps.keys) and np.array_equal(gv[u][:n], ps.values), f"{kind} unit {u}"
