@@ -261,3 +261,123 @@ def test_formed_tiles_of_whole_slots(grp, tq, S, cap, theta):
         h.log(f"{form} rows: err {err:.2e}, lse {el:.2e}")
         assert err <= h.READOUT_ATOL and el <= h.LSE_ATOL
         pair.gpu.read_pseudo()   # writes the rows
+
+
+def _seeking_query(pair, pseudo, seed):
+    """A query of which every second row of the sampled units looks for one key,
+    the keys spread over the context from first to last: its logit, 25, is far
+    above those before it, so a row's running maximum grows late."""
+    q = pair.query(np.random.default_rng(seed))
+    wl, ora = pair.wl, pair.oracle[0]
+    grp = wl.num_q_heads // wl.num_kv_heads
+    rows = wl.query_tokens * grp
+    for i, u in enumerate(pair.sample):
+        l, h = divmod(u, wl.num_kv_heads)
+        k = ora.context(i, pseudo[i])[0]
+        for r in range(0, rows, 2):
+            key = k[r * (len(k) - 1) // max(rows - 1, 1)]
+            q[l, r // grp, h * grp + r % grp] = key * (25.0 * np.sqrt(128.0) / float(key @ key))
+    return W.quantize(q, wl.kv_dtype)
+
+
+def _check_readout(h, pair, q, form):
+    """The device's readout of the sampled units against the oracle's.  Weights are
+    rounded to bf16 and their sum is taken over the rounded ones, so where a few
+    equal rows hold all the mass the lse errs by up to bf16's unit roundoff, 2^-8
+    (float32's own errors stay below 1e-4)."""
+    import torch
+    wl, grp = pair.wl, pair.wl.num_q_heads // pair.wl.num_kv_heads
+    o, lse = pair.gpu.attend(0, torch.from_numpy(q).to("cuda", torch.bfloat16).contiguous())
+    torch.cuda.synchronize()
+    go, gl = o.float().cpu().numpy(), lse.cpu().numpy()
+    oo, ol = pair.oracle[0].attend(q, wl.num_kv_heads, pair.oracle[0].synthesize())
+    worst, worst_lse = 0.0, 0.0
+    for u in pair.sample:
+        l, kvh = divmod(u, wl.num_kv_heads)
+        heads = slice(kvh * grp, (kvh + 1) * grp)
+        worst = max(worst, float(np.abs(go[l][:, heads] - oo[l][:, heads]).max()))
+        worst_lse = max(worst_lse, float(np.abs(gl[l][:, heads] - ol[l][:, heads]).max()))
+    h.log(f"{form} rows: err {worst:.2e}, lse {worst_lse:.2e}")
+    assert worst <= h.READOUT_ATOL and worst_lse <= 2.0 ** -8 + 1e-4
+
+
+# One workgroup (two in the first case) for a kv head's whole context, so that it
+# goes through at least four formed tiles: of 8 slots, 40 and 27 a split; of 5, 9,
+# 4 and 8 slots with 5, 5, 2 and 5 in the last; 105 near keys, or 105 + 37 x 8
+# .. 53 x 5 written rows, are two, five and more loaded tiles.  Rows 40 (two waves
+# per 32 rows, a key half each) and 136 (a wave per 32)
+@pytest.mark.parametrize("units,grp,tq,S,cap,theta,opt", [
+    (128, 8, 5, 8, 67, 0.0, {}), (192, 8, 5, 5, 53, 1e4, {}), (192, 8, 17, 7, 41, 1e4, {"ema": True}),
+    (192, 8, 17, 16, 18, 1e4, {}), (192, 8, 5, 16, 18, 0.0, {"ema": True}), (192, 8, 5, 8, 37, 0.0, {"use_pq": False}),
+    (192, 8, 17, 5, 53, 0.0, {"ema": True})])
+def test_formed_tiles_in_turn(units, grp, tq, S, cap, theta, opt):
+    """bf16 readout of more than 32 query rows per kv head, several tiles of each
+    kind to a workgroup: staging, centres, rotation tables and tiles three, two and
+    one ahead, the running maximum growing late.  Formed rows and then written
+    ones, against the oracle on three units."""
+    h = H()
+    wl = W.WORKLOADS["7b"].with_(num_layers=units // 8, num_kv_heads=8, num_q_heads=8 * grp, grid_h=5, grid_w=7,
+                                 frames=8, window_frames=3, capacity=cap, query_tokens=tq)
+    h.log(f"case: formed tiles in turn units {units} rows {grp * tq} S={S} K={cap} theta {theta} {opt}")
+    pair = _stream(h, wl, sample=[0, units // 2 + 3, units - 1], cb_samples=64, cb_iters=2, S=S, B=max(32, S),
+                   rope_theta=theta, **opt)
+    q = pair.query(np.random.default_rng(S)) if theta else _seeking_query(pair, pair.oracle[0].synthesize(), S)
+    pair.synthesize()
+    _check_readout(h, pair, q, "formed")
+    pair.check_rows()   # writes the rows
+    _check_readout(h, pair, q, "written")
+
+
+# One workgroup of eight waves a kv head: 588 near keys (and 3 x 52 written rows) in
+# tiles of 32 give every wave two or three loaded tiles, 52 slots at 5, 4 and 2 to a
+# tile one to four formed ones; half the waves take the formed ones first.  Rows 7,
+# 32, 7 and 21
+@pytest.mark.parametrize("grp,tq,S,theta,opt", [(7, 1, 5, 0.0, {"ema": True}), (8, 4, 8, 0.0, {}), (7, 1, 16, 1e4, {}),
+                                                (7, 3, 3, 0.0, {}), (7, 1, 8, 0.0, {"use_pq": False})])
+def test_few_rows_many_tiles(grp, tq, S, theta, opt):
+    """bf16 readout of at most 32 query rows, several tiles of each kind to a wave:
+    the next tile's loads under this one's products, the wave's LDS used again,
+    the running maximum growing late.  Formed rows and then written ones, against
+    the oracle on three units."""
+    h = H()
+    units, cap = 192, 52
+    wl = W.WORKLOADS["7b"].with_(num_layers=units // 8, num_kv_heads=8, num_q_heads=8 * grp, grid_h=14, grid_w=14,
+                                 frames=5, window_frames=3, capacity=cap, query_tokens=tq)
+    h.log(f"case: few rows, many tiles rows {grp * tq} S={S} theta {theta} {opt}")
+    pair = _stream(h, wl, sample=[0, units // 2 + 3, units - 1], cb_samples=64, cb_iters=2, S=S, B=max(32, S),
+                   rope_theta=theta, **opt)
+    q = pair.query(np.random.default_rng(S)) if theta else _seeking_query(pair, pair.oracle[0].synthesize(), S)
+    pair.synthesize()
+    _check_readout(h, pair, q, "formed")
+    pair.check_rows()   # writes the rows
+    _check_readout(h, pair, q, "written")
+
+
+# 588 near keys + 60 x 16 or 60 x 3 rows: 49 and 24 tiles of 32 over at most 16
+# splits, three or four and two to a wave, the last of 12 keys; rows 33 and 7
+@pytest.mark.parametrize("grp,tq,S", [(3, 11, 16), (7, 1, 3)])
+def test_float32_readout_many_tiles(grp, tq, S):
+    """float32 KV, several tiles to a wave, the running maximum growing late.  A dot
+    product goes through at most 24 roundings, so a logit errs by less than e = 24
+    2^-24 |q| |k| / sqrt(D); its weight by twice that.  A sum over a wave's keys and
+    the splits' is a chain of at most 4 x 32 + 16 roundings, 192 with those of the
+    exponentials and the rescaling."""
+    import torch
+    h = H()
+    wl = W.WORKLOADS["tiny"].with_(num_layers=2, num_kv_heads=2, num_q_heads=2 * grp, grid_h=14, grid_w=14, frames=5,
+                                   window_frames=3, capacity=60, query_tokens=tq)
+    h.log(f"case: float32 readout, many tiles rows {grp * tq} S={S}")
+    pair = _stream(h, wl, S=S)
+    pseudo = pair.oracle[0].synthesize()
+    q = _seeking_query(pair, pseudo, S)
+    oo, ol = pair.oracle[0].attend(q, wl.num_kv_heads, pseudo)
+    pair.gpu.synthesize(0)
+    o, lse = pair.gpu.attend(0, torch.from_numpy(q).to("cuda").contiguous())
+    torch.cuda.synchronize()
+    ctx = [pair.oracle[0].context(i, ps) for i, ps in enumerate(pseudo)]
+    kmax = max(float(np.linalg.norm(c[0], axis=1).max()) for c in ctx)
+    vmax = max(float(np.abs(c[1]).max()) for c in ctx)
+    e = 24 * 2.0 ** -24 * float(np.linalg.norm(q, axis=-1).max()) * kmax / np.sqrt(128.0)
+    err, el = np.abs(o.cpu().numpy() - oo).max(), np.abs(lse.cpu().numpy() - ol).max()
+    h.log(f"readout err {err:.2e} (bound {(2 * e + 192 * 2.0 ** -24) * vmax:.1e}), lse err {el:.2e} ({e + 192 * 2.0 ** -24:.1e})")
+    assert err <= (2 * e + 192 * 2.0 ** -24) * vmax and el <= e + 192 * 2.0 ** -24
