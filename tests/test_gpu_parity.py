@@ -332,6 +332,35 @@ def test_ema_centres_lists(dtype, grid, K, C, streams):
     pair.check_bank(bitwise=True)
 
 
+@pytest.mark.parametrize("ema", [False, True])
+def test_codes_of_overflowing_residuals(ema):
+    """Residuals whose squares overflow float32 are equally far from every
+    codeword: the lowest one, as with any tie.  Both encoders (the screen's
+    and, with EMA centres, the aggregation's) against the oracle's counts."""
+    import torch
+    from oracle import protokv_oracle as O
+    h = H()
+    wl = W.WORKLOADS["7b"].with_(num_layers=1, num_kv_heads=2, num_q_heads=2, grid_h=5, grid_w=7, frames=6,
+                                 window_frames=1, capacity=40, query_tokens=1, kv_dtype="fp32")
+    h.log(f"case: overflowing residuals ema={ema}")
+    p = h.oracle_params(wl, ema=ema)
+    cb = W.make_codebooks(wl, samples=256, iters=3)
+    gpu, ora, host = h.pk.ProtoKV(h.gpu_config(wl, p), cb), O.OracleStream(p, [0, 1], cb), W.HostStream(wl)
+    for f in range(wl.frames):
+        k, v = host.next_frame()
+        if f >= 3:
+            v[0, 3 + f, 5], v[1, 20, 70:100] = 3e19, -3e19
+        with np.errstate(over="ignore", invalid="ignore"):
+            ora.append_frame(k, v)
+        gpu.append_frame([0], *(torch.from_numpy(x).to("cuda").view(1, 1, 2, 35, 128).contiguous() for x in (k, v)))
+        gpu.fold()
+    bank = gpu.read_bank(0)
+    for u in (0, 1):
+        for name, want in (("n", ora.banks[u].n), ("n_res", ora.banks[u].n_res), ("hist_k", ora.banks[u].hist_k),
+                           ("hist_v", ora.banks[u].hist_v)):
+            assert np.array_equal(bank[name][u].astype(np.int64), want), f"unit {u} {name}"
+
+
 @pytest.mark.parametrize("wl_name,theta,grid", [("7b", 1e4, 6), ("7b", 1e6, 6), ("7b", 1e4, 24), ("tiny", 1e4, 8)])
 def test_rope_readout(wl_name, theta, grid):
     """Rotary positions in the readout: near keys at their stream positions,
