@@ -17,7 +17,6 @@ constexpr int SMAX = 16;   // pseudo-tokens per prototype
 constexpr int TMAX = 1024; // tokens per frame
 constexpr int MAXB = 64;   // streams per launch batch
 constexpr int MAX_SPLITS = 16;  // attention context splits (partials storage)
-constexpr int MAX_RBLOCKS = 2;  // query-row blocks of 256 per kv head
 constexpr int F32_KEYS = 32;    // keys per tile of the float32 readout
 constexpr int NUM_SIMD = 1024;  // 256 compute units of four SIMDs
 constexpr int KMAX = 65535;     // prototype slots per unit (slot ids fit 16 bits)

@@ -603,6 +603,11 @@ __device__ __forceinline__ void decode_join(const E (&pa)[SM], const E (&pb)[SM]
 // (112 units x 256 slots: 32 -> 17 us; 64 slots 25 -> 7 us; S = 16 on 2 000
 // slots, two lanes and merge pops before, 63 -> 13.5 us).  Two waves a SIMD, as the
 // LDS allows: with 262 registers S > 8 had one (112 x 256, S = 16, 49 -> 38 us).
+// Those are times of one query after another.  A wave runs straight through its
+// code once, so a query after eight folds, or with other data through the caches
+// since, waits for instructions too (by events, S = 8: 64 slots 10 and 17 us, 28 and
+// 42 by the kernels before; 112 x 256 17 and 25, before 35 and 54; 256 x 1 024 90 and
+// 121, before 114 and 139; S = 16, 112 x 256, 37 and 51, before 88 and 136).
 template <int SM>
 __global__ __launch_bounds__(256, 2) void k_decode(Dims dm, Workspace ws, int sid, int n_active, int centres) {
   constexpr int SPW = 16;  // slots per wave
@@ -1307,8 +1312,6 @@ constexpr int AT_TILE_BYTES = AT_KEYS * D * 2;   // one K or V tile, 16 KB
 typedef short v4i16 __attribute__((ext_vector_type(4)));
 typedef short v8i16 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) v4i16 lds_v4i16;
-typedef __attribute__((address_space(3))) void lds_void;
-typedef __attribute__((address_space(1))) const void gbl_void;
 
 // Barrier for LDS traffic only: waits for this wave's LDS operations, not
 // for its outstanding global loads (the tiles in flight).  The asm memory
@@ -2257,7 +2260,6 @@ __global__ __launch_bounds__(A32_W * 64, 2) void k_attend_rows32(Dims dm, Worksp
   }
 }
 
-// Combines the splits of each query row: O = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s.
 // Combines the splits' partials of output row r, dims 4 d4 .. 4 d4 + 3, of
 // kv head u: O = sum_s w_s O_s / sum_s w_s l_s with w_s = 2^(m_s - max m).
 // NSP: the number of splits when known at compile time (0: aa.splits).
@@ -2340,9 +2342,9 @@ __global__ __launch_bounds__(256) void k_attend_merge(Dims dm, Workspace ws, Att
 // A dot product is the sum of eight 16-dim chains, four and four: its rounding
 // error is that of a pairwise sum (one chain of 64 steps would carry several
 // times as much into the exponent).  Bound by the float32 matrix rate: 32 kv
-// heads x 224 rows x 3 616 keys (13.3 GFLOP) take 149 us, of which the matrix
-// cores are busy 56% (one wave per query row with a shuffled dot product per key
-// took 4 311 us); its error against 64 bits fell from 2.3e-6 to 7e-7.
+// heads x 224 rows x 3 616 keys (13.3 GFLOP) take 149 us (157 under the counters,
+// by which the matrix cores are busy 54% of it; one wave per query row with a
+// shuffled dot product per key took 4 311 us); its error against 64 bits fell from 2.3e-6 to 7e-7.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) const f32x4 gbl_f32x4;
 
