@@ -1594,7 +1594,9 @@ __global__ __launch_bounds__(NW * 64, 1) void k_attend_bf16(Dims dm, Workspace w
   // and everything it derives from its row (centre, tuple, codebook and store
   // addresses) is computed once (tiles of 64 rows across slots, derived anew for
   // every 16 bytes: high resolution 740 us against 614, 448 rows over K = 1024
-  // 507 against 443, 7B 95 against 89).  The inputs of a tile (the
+  // 507 against 443, 7B 95 against 89; that is S = 8, where no row stays empty.
+  // Least is left of it at S = 11, 55 rows a tile: 448 rows over K = 1024, before
+  // whole slots and with all that has changed since, 600 -> 586, at S = 13 694 -> 657).  The inputs of a tile (the
   // bank rows' float32 sums, 1 KiB per slot, and decode records of its slots)
   // go by DMA into one of three staging buffers three tiles ahead; two tiles
   // ahead the sums are turned into centres in place.  Iteration t: wait for
@@ -2538,7 +2540,9 @@ hipError_t launch_attend(const Dims& dm, const Workspace& ws, const AttendArgs& 
     hipLaunchKernelGGL(k_attend_f32, dim3((items + 3) / 4), dim3(256), 0, st, dm, ws, aa, rows, rblocks);
   } else {
     // 8 waves per workgroup: 256 query rows, or at most 128 rows with the
-    // tiles' key halves split between wave pairs
+    // tiles' key halves split between wave pairs; at most 32 rows, the one block
+    // a wave holds, a wave per tile (28 rows, 112 x 256 slots, S = 8: 66 us with key
+    // halves, 34 so; 32 rows, 256 x 2 048: 642 and 253, and 33 rows there 509 now)
     const int rblocks = (rows + AT_ROWS - 1) / AT_ROWS;
     if (rows <= 32)
       hipLaunchKernelGGL(k_attend_rows32, dim3(dm.units * aa.splits), dim3(A32_W * 64), 0, st, dm, ws, aa, rows);
